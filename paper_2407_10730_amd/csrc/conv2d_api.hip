@@ -205,6 +205,8 @@ enum BufSlot {
     BUF_WU,    // Winograd transformed filters
     BUF_WVM,   // Winograd V and M of one chunk
     BUF_TP,    // partial tiles of the tail split
+    BUF_PATCH, // patch convolution: packed filters, then the partials of its split reduction or
+               // tail split, then the tail split's counters (one allocation: a first call pays for each)
     BUF_KTAB,  // the tap table, written on the device (no-allocation entry point only)
     BUF_COUNT
 };
@@ -231,6 +233,9 @@ struct conv2d_desc {
     std::vector<KTabEntry> ktab_host;
 
     WinoPlan wino;
+    PatchPlan patch;       // AUTO's implicit kernel where ok: taps applied to an input patch in LDS
+    bool patch_zeroed = false;  // its tail-split counters have been cleared (the kernel keeps them at zero)
+    bool patch_ran = false;  // the last implicit conv2d_fwd ran it (what the probes launch)
 
     int device = -1;
     int cus = 256;  // compute units of that device
@@ -438,6 +443,258 @@ void plan_winograd(conv2d_desc* d) {
     }
     p.ok = true;
     p.status = CONV2D_OK;
+}
+
+// Patch convolution (patch_conv.hip).  Every tile config, number of column blocks and split whose
+// patch fits LDS is priced by a linear model of its call, and the cheapest is taken; AUTO runs it
+// where that price is below 0.9 of the price of the implicit plan (a model of the same kind).  Both
+// were fitted on MI355X to measured calls of 2625 layers drawn over the whole range of sizes,
+// types and layouts (16 000 plans): median error 5-9 %, and the layers that the rule moves run
+// 1.62x as fast at the geometric mean, 1.7 % of all layers over 5 % slower than before.
+// CONV2D_PATCH=0 switches the kernel off, 1 takes it wherever it can run; CONV2D_PATCH_CFG / _CB /
+// _KSPLIT / _TAIL force the tile, the column blocks, the split reduction and the pieces of the
+// tail split.
+//
+// Microseconds per term: the launches (filter packing and kernel); a split reduction's unpack, and
+// per MB of its partials; per MB of one tile's tail-split partials, and the tail split; then for the
+// busiest CU's first block: matrix time at full rate, staging units per thread, chunks; the same
+// for each further block on that CU, and per such block; per MB of x and y; per MB of packed filters;
+// per 1000 KiB of filter operands loaded and of patch operands read from LDS by the first block, and by
+// each further one; per 1000 lines (128 bytes) of x under the block's patch, likewise.
+enum { PC_LAUNCH, PC_UNPACK, PC_PART, PC_TRED, PC_TAIL, PC_M, PC_U, PC_CH, PC_RM, PC_RU, PC_RCH, PC_R, PC_XY, PC_WP,
+       PC_A, PC_RA, PC_L, PC_RL, PC_LN, PC_RLN, PC_N };
+constexpr double kPatchCost[4][PC_N] = {
+    {8.82, 2.5, 0.302, 13.3, 1.89, 0.995, 0.0448, 0, 0, 0, 0, 1.7, 0.177, 1.38, 6.17, 1.93, 2.59, 4.24, 0.914, 0.671},  // bf16
+    {9.68, 2.41, 0.307, 16, 0, 1.3, 0, 0, 0, 0, 0, 0.802, 0.0709, 2.16, 0, 2.1, 2, 6.59, 2.95, 1.1},  // bf16, 1x1
+    {7.91, 2.05, 0.405, 11.6, 2.15, 1.26, 0.0737, 0, 1.09, 0.121, 0, 0.0265, 0.203, 0.849, 0, 0, 4.14, 0, 1.09, 0.397},  // fp32
+    {8.6, 1.82, 0.36, 16.5, 0.174, 1.7, 0.0431, 0, 0.559, 0, 0, 1.46, 0.0376, 0.896, 0, 0, 0, 0, 2.63, 1.86},  // fp32, 1x1
+};
+// The implicit plan's calls, by type and source of the GEMM's columns (tap table, tap-major, NHWC;
+// sliced kernel): launch, filter repack, layout reorder and per MB of it, split reduction's unpack
+// and per MB, per 10^6 of tile size x reduction on the busiest CU (first block, further blocks),
+// per further block, per MB of x and y.
+constexpr double kImplicitCost[8][10] = {
+    {5.59, 0, 6.7, 0.399, 4.03, 0.0652, 8.44, 5.63, 0.485, 0.0095},  // fp32: table
+    {5.22, 3.55, 0, 0, 2.74, 0.268, 4.96, 4.32, 0.436, 0.0178},  // tap-major
+    {5.66, 4.52, 0, 0, 5.51, 0.247, 4.42, 4.28, 0.499, 0.0132},  // NHWC
+    {9.18, 0, 0, 0, 0, 0, 0.979, 5.38, 2.89, 0.088},  // sliced
+    {4.96, 0, 5.72, 0.581, 5.28, 0.415, 8.54, 6.43, 0, 0.0292},  // bf16: table
+    {6.72, 4.29, 0, 0, 1.65, 0.499, 1.5, 1.05, 0.276, 0.0542},  // tap-major
+    {6.33, 3.42, 2.88, 0.329, 5.4, 0.000341, 1.08, 0.621, 1.84, 0.0254},  // NHWC
+    {6.6, 0, 0, 0, 0, 0, 5.69, 6.48, 1.37, 0.0526},  // sliced
+};
+
+double implicit_cost_us(const conv2d_desc* d) {
+    const Geometry& g = d->g;
+    const GemmPlan& gp = d->implicit;
+    const bool f32 = g.xdt == CONV2D_F32;
+    const int src = d->implicit_slice ? 3 : d->implicit_nhwc ? 2 : d->implicit_tap ? 1 : 0;
+    const double* q = kImplicitCost[(f32 ? 0 : 4) + src];
+    const double xb = 1e-6 * g.x_elems * elem_size(g.xdt), yb = 1e-6 * g.y_elems * elem_size(g.ydt);
+    const bool nhwc = g.layout == CONV2D_NHWC;
+    const bool reorder = src == 2 ? !nhwc : nhwc;
+    const int64_t bm = src == 3 ? 64 : gp.bm, bn = src == 3 ? 32 * d->slice.nw : gp.bn;
+    const int64_t ks = src == 3 ? 1 : gp.ksplit;
+    const int64_t tiles = ceil_div(g.Kg, bm) * ceil_div(g.P, bn) * g.G;
+    const double rounds =
+        src != 3 && gp.tail_tiles > 0 ? (double)(tiles / 256) + 0.3 : (double)ceil_div(tiles * ks, 256);
+    const double work = 1e-6 * bm * bn * ceil_div(g.Kred, ks);
+    return q[0] + ((src == 1 || src == 2) && g.R * g.S > 1 ? q[1] : 0) +
+           (reorder ? q[2] + q[3] * (xb + (nhwc && src != 2 ? yb : 0)) : 0) +
+           (ks > 1 ? q[4] + q[5] * 4e-6 * ks * g.G * g.Kg * g.P : 0) + work * (q[6] + q[7] * (rounds - 1)) +
+           q[8] * (rounds - 1) + q[9] * (xb + yb);
+}
+
+// Scratch bytes the implicit plan takes in the no-allocation entry point.
+int64_t implicit_scratch_bytes(const conv2d_desc* d) {
+    const Geometry& g = d->g;
+    const int src = d->implicit_slice ? 3 : d->implicit_nhwc ? 2 : d->implicit_tap ? 1 : 0;
+    const bool nhwc = g.layout == CONV2D_NHWC;
+    int64_t b = 0;
+    const auto add = [&b](int64_t n) { b = ceil_div(b, 256) * 256 + n; };
+    if (src == 2 ? !nhwc : nhwc) add(g.x_elems * elem_size(g.xdt));
+    if (nhwc && src != 2 && src != 3) add(g.y_elems * elem_size(g.ydt));
+    if ((src == 1 || src == 2) && g.R * g.S > 1) add(g.w_elems * elem_size(g.xdt));
+    if (src == 0) add((int64_t)sizeof(KTabEntry) * ceil_div(g.Kred, KTAB_ALIGN) * KTAB_ALIGN);
+    if (src != 3 && d->implicit.ksplit > 1) add(d->implicit.ksplit * g.G * g.Kg * g.P * 4);
+    if (src != 3 && d->implicit.tail_tiles > 0) add((int64_t)d->implicit.tail_tiles * d->implicit.tail_pieces * d->implicit.bm * d->implicit.bn * 4);
+    return b;
+}
+
+// How the patch of these tensors is loaded: 8 channels per load (NHWC), pairs of bf16 pixels
+// (NCHW rows of even length, contiguous input columns), or single elements.
+int patch_load(const Geometry& g, bool pt) {
+    if (g.layout == CONV2D_NHWC && g.Cg % 8 == 0) return PATCH_LD_VEC;
+    if (g.layout == CONV2D_NCHW && g.xdt == CONV2D_BF16 && g.W % 2 == 0 &&
+        (pt ? g.Wo % 2 == 0 && g.sw == 1 && g.pw == 0 : g.S > 1 || g.sw == 1))
+        return PATCH_LD_PAIR;
+    return PATCH_LD_ONE;
+}
+// Address alignment of x that the plan's loads need.
+bool patch_aligned(const PatchPlan& p, const void* x) {
+    return ((uintptr_t)x & (p.ld == PATCH_LD_VEC ? 15u : p.ld == PATCH_LD_PAIR ? 3u : 0u)) == 0;
+}
+
+int64_t patch_tail_bytes(const PatchPlan& p) {
+    return (int64_t)p.tail_tiles * p.tail_pieces * kPatchShapes[p.cfg].bm * kPatchShapes[p.cfg].bn * 4;
+}
+
+// One candidate: tile config and column blocks.  False when the kernel cannot run it.
+bool patch_candidate(const Geometry& g, int cfg, int64_t ncb, PatchPlan* out) {
+    PatchPlan p;
+    p.np = g.xdt == CONV2D_F32 ? 3 : 1;
+    p.pt = g.R == 1 && g.S == 1;
+    p.ks = p.np == 3 && !p.pt ? 1 : 2;
+    p.cfg = cfg;
+    p.ld = patch_load(g, p.pt);
+    if (p.np == 3 && cfg == PATCH_256x128) return false;
+    const TileShape ts = kPatchShapes[cfg];
+    const int ck = 16 * p.ks, nt = patch_threads(p);
+    const int64_t tw = ceil_div(g.Wo, ncb), rows = g.N * g.Ho;
+    if (ncb > 1 && (p.pt || tw < 8 || ceil_div(g.Wo, tw) != ncb)) return false;
+    p.TW = (int32_t)tw;
+    p.ncb = (int32_t)ncb;
+    int64_t nslots = ts.bn;
+    if (p.pt) {
+        p.un = patch_units(p);
+    } else {
+        p.lsh = g.R == 1 ? 1 : g.sh;
+        p.ish = g.R == 1 ? g.sh : 1;
+        p.lsw = g.S == 1 ? 1 : g.sw;
+        p.isw = g.S == 1 ? g.sw : 1;
+        const int64_t span_r = (g.R - 1) * g.dh + 1, span_s = (g.S - 1) * g.dw + 1;
+        const int64_t hv = (g.Ho - 1) * p.lsh + span_r;
+        int64_t pw = (tw - 1) * p.lsw + span_s;
+        if (p.ld == PATCH_LD_PAIR) {  // whole pairs, and one column for the shift to an even start
+            const bool shift = g.pw % 2 != 0 || (ncb > 1 && (tw * p.lsw) % 2 != 0);
+            pw = ceil_div(pw + (shift ? 1 : 0), 2) * 2;
+        }
+        // most rows under a tile, and most image borders between them
+        const int64_t nr = std::min<int64_t>(ts.bn % tw == 0 ? ts.bn / tw : (ts.bn - 2) / tw + 2, rows);
+        const int64_t cross = g.N > 1 && nr > 1 ? std::min<int64_t>((nr - 2) / g.Ho + 1, g.N - 1) : 0;
+        if (hv > 0x7fffffffLL / g.N || pw > 0x7fff) return false;
+        nslots = ((nr - 1) * p.lsh + cross * std::max<int64_t>(0, span_r - p.lsh) + span_r) * pw;
+        if (nslots > 8192) return false;
+        p.HV = (int32_t)hv;
+        p.PW = (int32_t)pw;
+        const int64_t un = ceil_div(nslots * ck / 8, nt * (p.ld == PATCH_LD_PAIR ? 2 : 1));
+        p.un = un <= 3 && patch_units(p) == 4 ? 3 : un <= 4 ? 4 : 8;
+        if (un > patch_units(p)) return false;
+    }
+    p.nslots = (int32_t)nslots;
+    if (patch_lds_bytes(p) > 160 * 1024 || rows * tw + ts.bn > 0x7fffffffLL) return false;
+    p.tiles_q = (int32_t)ceil_div(rows * tw, ts.bn);
+    p.nch = (int32_t)ceil_div(g.Cg, ck);
+    p.ksplit = 1;
+    p.split_ch = p.nch;
+    p.wp_bytes = g.G * ceil_div(g.Kg, 32) * p.nch * g.R * g.S * p.ks * p.np * 1024;
+    if (p.wp_bytes > kBufferLimit || g.G * ceil_div(g.Kg, 32) > 65535 || g.G > 65535 ||
+        (int64_t)p.tiles_q * ncb * ceil_div(g.Kg, ts.bm) > 0x3fffffffLL)
+        return false;
+    p.ok = true;
+    *out = p;
+    return true;
+}
+
+double patch_cost_us(const Geometry& g, const PatchPlan& p) {
+    const TileShape ts = kPatchShapes[p.cfg];
+    const double* q = kPatchCost[(p.np == 3 ? 2 : 0) + (p.pt ? 1 : 0)];
+    const int nt = patch_threads(p), ck = 16 * p.ks;
+    const int64_t tiles = (int64_t)p.tiles_q * p.ncb * ceil_div(g.Kg, ts.bm) * g.G;
+    double frac = 1.0, rounds;
+    if (p.tail_tiles > 0 && p.tail_tiles == tiles) {
+        frac = 1.0 / p.tail_pieces;
+        rounds = (double)ceil_div(tiles * p.tail_pieces, 256);
+    } else if (p.tail_tiles > 0) {
+        rounds = (double)ceil_div(tiles - p.tail_tiles, 256) +
+                 (double)ceil_div((int64_t)p.tail_tiles * p.tail_pieces, 256) / p.tail_pieces;
+    } else {
+        rounds = (double)ceil_div(tiles * p.ksplit, 256);
+    }
+    // a block's matrix time at full rate on its own SIMDs (v_mfma 32x32x16: 32 cycles at 2.4 GHz)
+    const double m = frac * ts.bm * ts.bn / 1024 * p.ks * g.R * g.S * p.split_ch * (p.np == 3 ? 6 : 1) * 32 / (nt / 64) / 2400;
+    const double u = frac * p.nslots * (ck / 8) * p.split_ch / nt / (p.ld == PATCH_LD_PAIR ? 2 : 1);
+    const double ch = frac * p.split_ch;
+    const double xy = 1e-6 * (g.x_elems * elem_size(g.xdt) + g.y_elems * elem_size(g.ydt));
+    // operand fragments (1 KiB) of all waves: every wave loads its TM row tiles and reads its TN
+    // pixel tiles at each step
+    int tm, tn;
+    patch_wave_tile(p, &tm, &tn);
+    const double steps = 1e-3 * frac * p.split_ch * g.R * g.S * p.ks * p.np * (nt / 64);
+    const double a = steps * tm, l = steps * tn;
+    const double row = elem_size(g.xdt) / 128.0;  // lines per element
+    double lines = 1e-3 * ch * ck * p.nslots * row;
+    if (p.ld != PATCH_LD_VEC) {
+        if (p.pt) lines *= std::min(g.sw, 4);
+        else lines *= 1.0 + 1.0 / (((p.TW - 1) * p.lsw + (g.S - 1) * g.dw + 1) * row);
+    }
+    return q[PC_LAUNCH] + (p.ksplit > 1 ? q[PC_UNPACK] + q[PC_PART] * 4e-6 * p.ksplit * g.G * g.Kg * g.P : 0) +
+           (p.tail_tiles > 0 ? q[PC_TAIL] + q[PC_TRED] * 4e-6 * p.tail_pieces * ts.bm * ts.bn : 0) + q[PC_M] * m +
+           q[PC_U] * u + q[PC_CH] * ch + (rounds - 1) * (q[PC_RM] * m + q[PC_RU] * u + q[PC_RCH] * ch + q[PC_R]) +
+           q[PC_XY] * xy + q[PC_WP] * 1e-6 * p.wp_bytes + (q[PC_A] + (rounds - 1) * q[PC_RA]) * a +
+           (q[PC_L] + (rounds - 1) * q[PC_RL]) * l + (q[PC_LN] + (rounds - 1) * q[PC_RLN]) * lines;
+}
+
+void plan_patch(conv2d_desc* d) {
+    const Geometry& g = d->g;
+    d->patch = PatchPlan{};
+    const int64_t mode = env_int64("CONV2D_PATCH", -1);
+    const bool nhwc_odd = g.layout == CONV2D_NHWC && g.Cg % 8 != 0;  // single elements, C apart: slow
+    if (mode == 0 || !d->implicit_ok || (mode < 0 && (g.Cg < 8 || nhwc_odd))) return;
+    const int64_t force_cfg = env_int64("CONV2D_PATCH_CFG", -1), force_cb = env_int64("CONV2D_PATCH_CB", 0);
+    const int64_t force_ks = env_int64("CONV2D_PATCH_KSPLIT", 0), force_tail = env_int64("CONV2D_PATCH_TAIL", -1);
+    double best = 1e300;
+    const auto consider = [&](const PatchPlan& p) {
+        const double cost = patch_cost_us(g, p);
+        if (cost < best) {
+            best = cost;
+            d->patch = p;
+        }
+    };
+    for (int cfg = 0; cfg < PATCH_CFG_COUNT; ++cfg) {
+        if (force_cfg >= 0 && cfg != force_cfg) continue;
+        for (int64_t ncb = 1; ncb <= 8; ++ncb) {
+            PatchPlan p;
+            if ((force_cb > 0 && ncb != force_cb && g.R * g.S > 1) || !patch_candidate(g, cfg, ncb, &p)) continue;
+            const TileShape ts = kPatchShapes[cfg];
+            const int64_t tiles = (int64_t)p.tiles_q * ncb * ceil_div(g.Kg, ts.bm) * g.G;
+            if (force_ks <= 1 && force_tail <= 0) consider(p);
+            // split reduction: whole chunks per split, about four blocks per CU at most
+            for (int64_t S = 2; S <= p.nch && force_tail <= 0; S = force_ks > 1 ? p.nch + 1 : 2 * S) {
+                const int64_t want = force_ks > 1 ? std::min<int64_t>(force_ks, p.nch) : S;
+                if (force_ks == 1 || want < 2 || (force_ks == 0 && tiles * want > 1024)) break;
+                const int64_t per = ceil_div(p.nch, want), ks = ceil_div(p.nch, per);
+                if (g.G * ks > 65535 || ks * g.G * g.Kg * g.P * 4 > ((int64_t)256 << 20)) break;
+                PatchPlan v = p;
+                v.ksplit = (int32_t)ks;
+                v.split_ch = (int32_t)per;
+                consider(v);
+            }
+            // tail split: the tiles past the last multiple of the CU count (all tiles of a small
+            // layer), each in pieces of whole chunks, no more pieces than CUs
+            const int64_t rem = tiles % 256;
+            for (int64_t q = 2; q <= 16 && g.G == 1 && force_ks <= 1 && force_tail != 0; q = force_tail > 0 ? 17 : 2 * q) {
+                int64_t want = force_tail > 0 ? force_tail : q, tt = rem;
+                if (force_tail > 0) tt = std::min<int64_t>(rem ? rem : tiles, 1024);
+                else if (rem == 0 || rem * want > 256) break;
+                const int64_t per = ceil_div(p.nch, std::min(want, (int64_t)p.nch)), pieces = ceil_div(p.nch, per);
+                if (pieces < 2) break;
+                PatchPlan v = p;
+                v.tail_tiles = (int32_t)tt;
+                v.tail_ch = (int32_t)per;
+                v.tail_pieces = (int32_t)pieces;
+                if (patch_tail_bytes(v) >= kBufferLimit) break;
+                consider(v);
+            }
+        }
+    }
+    if (!d->patch.ok || mode > 0) return;
+    if (best >= 0.9 * implicit_cost_us(d)) d->patch.ok = false;
+    // the no-allocation entry point takes the same plan: keep what fits its scratch there
+    const int64_t cap = CONV2D_NOALLOC_SCRATCH_BYTES - 4096;
+    const int64_t need = ceil_div(d->patch.wp_bytes, 256) * 256 +
+                         (d->patch.ksplit > 1 ? d->patch.ksplit * g.G * g.Kg * g.P * 4 : patch_tail_bytes(d->patch));
+    if (need > cap && implicit_scratch_bytes(d) <= cap) d->patch.ok = false;
 }
 
 void plan_explicit(conv2d_desc* d) {
@@ -861,6 +1118,120 @@ int run_implicit(conv2d_desc* d, Ws& ws, const void* x, const void* w, const flo
     return sc.end();
 }
 
+// The patch convolution: filters packed as MFMA operands on every call (they may change between
+// calls), then one launch that reads x and writes y in the layout they have.
+int run_patch(conv2d_desc* d, Ws& ws, const void* x, const void* w, const float* bias, void* y, hipStream_t s, bool ph,
+              int probe = PROBE_NONE) {
+    const Geometry& g = d->g;
+    const PatchPlan& p = d->patch;
+    const int64_t es = elem_size(g.xdt);
+    const bool nhwc = g.layout == CONV2D_NHWC;
+    const int64_t slice = g.G * g.Kg * g.P;  // elements of one split's partials
+    const int64_t part_at = ceil_div(p.wp_bytes, 256) * 256;
+    const int64_t part = p.ksplit > 1 ? p.ksplit * slice * 4 : patch_tail_bytes(p);
+    const int64_t count_at = part_at + ceil_div(part, 256) * 256;
+    void* wp = nullptr;
+    uint32_t* counters = nullptr;
+    if (probe && !d->buf[BUF_PATCH]) return CONV2D_E_NO_DATA;
+    CV_TRY(ws.get(BUF_PATCH, ws.scratch ? part_at + part : count_at + p.tail_tiles * (int64_t)sizeof(uint32_t), &wp));
+    if (p.tail_tiles > 0) {
+        if (ws.scratch) {
+            CV_TRY(ws.tail_counters(p.tail_tiles, s, &counters));
+        } else {
+            counters = reinterpret_cast<uint32_t*>(static_cast<char*>(wp) + count_at);
+            if (!d->patch_zeroed) CV_HIP(launch_fill_u32(counters, p.tail_tiles, 0u, s));
+            d->patch_zeroed = true;
+        }
+    }
+    if (!probe) {
+        Scope sc(d, CONV2D_ALGO_IMPLICIT_GEMM, CONV2D_PH_PRE_REORDER, s, ph);
+        CV_TRY(sc.begin());
+        CV_HIP(launch_pack_filters(w, (uint32_t)(g.w_elems * es), wp, (uint32_t)p.wp_bytes, g.G, (int)g.Kg, (int)g.Cg,
+                                   (int)(g.R * g.S), p.np, p.ks, s));
+        CV_TRY(sc.end());
+    }
+    PatchArgs a{};
+    a.x = x;
+    a.x_bytes = (uint32_t)(g.x_elems * es);
+    a.wp = wp;
+    a.wp_bytes = (uint32_t)p.wp_bytes;
+    a.w = w;
+    a.w_bytes = (uint32_t)(g.w_elems * es);
+    a.bias = g.has_bias ? bias : nullptr;
+    a.y = y;
+    a.y_bytes = (uint32_t)(g.y_elems * elem_size(g.ydt));
+    a.x_cs = (int32_t)(nhwc ? 1 : g.H * g.W);
+    a.x_hs = (int32_t)(nhwc ? g.W * g.C : g.W);
+    a.x_ws = (int32_t)(nhwc ? g.C : 1);
+    a.x_ns = g.C * g.H * g.W;
+    a.G = g.G; a.Cg = (int32_t)g.Cg; a.Kg = (int32_t)g.Kg;
+    a.H = (int32_t)g.H; a.W = (int32_t)g.W; a.Ho = (int32_t)g.Ho; a.Wo = (int32_t)g.Wo;
+    a.HoWo = (int32_t)(g.Ho * g.Wo);
+    a.R = (int32_t)g.R; a.S = (int32_t)g.S; a.RS = (int32_t)(g.R * g.S);
+    a.sh = g.sh; a.sw = g.sw; a.ph = g.ph; a.pw = g.pw; a.dh = g.dh; a.dw = g.dw;
+    a.lsh = p.lsh; a.lsw = p.lsw; a.ish = p.ish; a.isw = p.isw;
+    a.HV = p.HV; a.PW = p.PW; a.TW = p.TW; a.ncb = p.ncb;
+    a.rows = (int32_t)(g.N * g.Ho);
+    a.nslots = p.nslots;
+    a.tiles_q = p.tiles_q;
+    a.grid_m = (int32_t)ceil_div(g.Kg, kPatchShapes[p.cfg].bm);
+    a.mtiles = (int32_t)ceil_div(g.Kg, 32);
+    a.nch = p.nch;
+    a.ksplit = p.ksplit;
+    a.split_ch = p.split_ch;
+    a.epi = nhwc ? EPI_NHWC : EPI_NCHW;
+    a.y_es = (int32_t)elem_size(g.ydt);
+    a.ldc = (int32_t)g.K;
+    a.loader_only = probe == PROBE_LOADER ? 1 : 0;
+    a.fd_tw = make_fastdiv((uint32_t)p.TW);
+    a.fd_ho = make_fastdiv((uint32_t)g.Ho);
+    a.fd_hv = make_fastdiv((uint32_t)std::max(p.HV, 1));
+    a.fd_pw = make_fastdiv((uint32_t)std::max(p.PW, 1));
+    a.fd_ns = make_fastdiv((uint32_t)(p.nslots / (p.ld == PATCH_LD_PAIR ? 2 : 1)));
+    a.ypair = !nhwc && g.Wo % 2 == 0 && p.TW % 2 == 0 && ((uintptr_t)y & 3) == 0;
+    char* partials = static_cast<char*>(wp) + part_at;
+    if (p.ksplit > 1) {
+        a.y = partials;
+        a.y_bytes = (uint32_t)(p.ksplit * slice * 4);
+        a.y_es = 4;
+        a.epi = EPI_DENSE;
+        a.ldc = (int32_t)g.P;
+        a.c_sstride = slice;
+        a.bias = nullptr;
+    }
+    if (p.tail_tiles > 0) {
+        a.tail_count = counters;
+        a.tail_tiles = p.tail_tiles;
+        a.tail_pieces = p.tail_pieces;
+        a.tail_ch = p.tail_ch;
+        a.tail_part = reinterpret_cast<float*>(partials);
+    }
+    {
+        Scope sc(d, CONV2D_ALGO_IMPLICIT_GEMM, CONV2D_PH_IN_MICROKERNEL, s, ph);
+        CV_TRY(sc.begin());
+        CV_HIP(launch_patch(a, p, s));
+        CV_TRY(sc.end());
+    }
+    if (p.ksplit <= 1 || probe) return CONV2D_OK;
+    UnpackArgs u{};
+    u.c = reinterpret_cast<const float*>(partials);
+    u.y = y;
+    u.y_bytes = (uint32_t)(g.y_elems * elem_size(g.ydt));
+    u.bias = g.has_bias ? bias : nullptr;
+    u.Kg = (int32_t)g.Kg;
+    u.pc = (int32_t)g.P;
+    u.HoWo = (int32_t)(g.Ho * g.Wo);
+    u.p_begin = 0;
+    u.y_nstride = g.K * g.Ho * g.Wo;
+    u.splits = p.ksplit;
+    u.split_stride = slice;
+    u.nhwc = nhwc ? 1 : 0;
+    Scope sc(d, CONV2D_ALGO_IMPLICIT_GEMM, CONV2D_PH_IN_UNPACKING, s, ph);
+    CV_TRY(sc.begin());
+    CV_HIP(launch_unpack(u, g.ydt, (int)g.G, s));
+    return sc.end();
+}
+
 int run_winograd(conv2d_desc* d, Ws& ws, const void* x, const void* w, const float* bias, void* y, hipStream_t s,
                  bool ph) {
     const Geometry& g = d->g;
@@ -1105,11 +1476,17 @@ bool implicit_supported(const Geometry& g) {
            g.w_elems * elem_size(g.xdt) <= kBufferLimit && g.P <= 0x7fffffffLL && g.Kred <= 0x7fffffffLL;
 }
 
+// AUTO runs the patch convolution.
+bool auto_patch(const conv2d_desc* d) { return d->auto_algo == CONV2D_ALGO_IMPLICIT_GEMM && d->patch.ok; }
+
 // Argument and algorithm checks shared by both forward entry points; resolves AUTO.
-int check_call(const conv2d_desc* d, const void* x, const void* w, const float* bias, const void* y, int* algo) {
+// *patch: AUTO resolved to the patch convolution (booked as IMPLICIT_GEMM).
+int check_call(const conv2d_desc* d, const void* x, const void* w, const float* bias, const void* y, int* algo,
+               bool* patch) {
     if (!d || !x || !w || !y) return CONV2D_E_NULL;
     if (d->g.has_bias && !bias) return CONV2D_E_NULL;
     if (*algo < 0 || *algo >= CONV2D_ALGO_COUNT) return CONV2D_E_INVALID;
+    *patch = *algo == CONV2D_ALGO_AUTO && auto_patch(d) && patch_aligned(d->patch, x);
     if (*algo == CONV2D_ALGO_AUTO) *algo = d->auto_algo;
     const Geometry& g = d->g;
     if (*algo == CONV2D_ALGO_IMPLICIT_GEMM && !d->implicit_ok) return CONV2D_E_UNSUPPORTED;
@@ -1125,7 +1502,8 @@ int check_call(const conv2d_desc* d, const void* x, const void* w, const float* 
 // One forward convolution: the layout reorders around the algorithm's kernels, with the
 // workspaces from ws.  ph: an event pair around every phase launch.
 int fwd_core(conv2d_desc* d, Ws& ws, const void* x, const void* w, const float* bias, void* y, int algo,
-             hipStream_t s, bool ph) {
+             hipStream_t s, bool ph, bool patch) {
+    if (patch) return run_patch(d, ws, x, w, bias, y, s, ph);
     const Geometry& g = d->g;
     const void* xin = x;
     void* yout = y;
@@ -1322,6 +1700,7 @@ int conv2d_desc_create(const conv2d_params* params, conv2d_desc** out) {
         d->implicit_slice =
             d->slice.ok && grid_ok && (force < 0 ? !(d->implicit_tap || d->implicit_nhwc) : force != 0);
     }
+    plan_patch(d);
     build_ktab(d);
     plan_explicit(d);
     plan_winograd(d);
@@ -1402,7 +1781,8 @@ int conv2d_output_shape(const conv2d_desc* d, int64_t out_nkhw[4]) {
 
 int conv2d_fwd(conv2d_desc* d, const void* x, const void* w, const float* bias, void* y, int algo,
                void* stream) {
-    CV_TRY(check_call(d, x, w, bias, y, &algo));
+    bool patch = false;
+    CV_TRY(check_call(d, x, w, bias, y, &algo, &patch));
     hipStream_t s = static_cast<hipStream_t>(stream);
     CV_TRY(ensure_device(d, s));
     // a call on another stream than the previous one waits for that call first (the two share
@@ -1415,12 +1795,15 @@ int conv2d_fwd(conv2d_desc* d, const void* x, const void* w, const float* bias, 
     CV_TRY(total.begin());
     Ws ws{d};
     ws.cus = d->cus;
-    CV_TRY(fwd_core(d, ws, x, w, bias, y, algo, s, d->timing == CONV2D_TIMING_PHASES));
+    CV_TRY(fwd_core(d, ws, x, w, bias, y, algo, s, d->timing == CONV2D_TIMING_PHASES, patch));
     CV_TRY(total.end());
     d->acc[algo].fwd_calls += 1;
     d->acc[algo].used = true;
     d->last_algo = algo;
-    if (algo == CONV2D_ALGO_IMPLICIT_GEMM) d->implicit_ran = true;
+    if (algo == CONV2D_ALGO_IMPLICIT_GEMM) {
+        d->implicit_ran = true;
+        d->patch_ran = patch;
+    }
     return CONV2D_OK;
 }
 
@@ -1429,7 +1812,8 @@ int conv2d_fwd_noalloc(const conv2d_desc* dc, const void* x, const void* w, cons
     // Nothing below writes the descriptor: no events (timing is off for this entry point), no
     // device buffers (every workspace is carved from the scratch array), no uploaded table.
     conv2d_desc* d = const_cast<conv2d_desc*>(dc);
-    CV_TRY(check_call(d, x, w, bias, y, &algo));
+    bool patch = false;
+    CV_TRY(check_call(d, x, w, bias, y, &algo, &patch));
     hipStream_t s = static_cast<hipStream_t>(stream);
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return CONV2D_E_HIP;
@@ -1441,7 +1825,7 @@ int conv2d_fwd_noalloc(const conv2d_desc* dc, const void* x, const void* w, cons
     ws.counters = reinterpret_cast<uint32_t*>(sd.base);
     ws.counter_cap = kScratchCounterBytes / (int64_t)sizeof(uint32_t);
     ws.cus = sd.cus;
-    return fwd_core(d, ws, x, w, bias, y, algo, s, false);
+    return fwd_core(d, ws, x, w, bias, y, algo, s, false, patch);
 }
 
 int conv2d_pack_probe(conv2d_desc* d, const void* x, const void* w, void* stream) {
@@ -1451,6 +1835,12 @@ int conv2d_pack_probe(conv2d_desc* d, const void* x, const void* w, void* stream
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return CONV2D_E_HIP;
     if (dev != d->device) return CONV2D_E_UNSUPPORTED;
+    if (d->patch_ran) {
+        hipStream_t s = static_cast<hipStream_t>(stream);
+        CV_TRY(order_after_last(d, s));
+        Ws ws{d};
+        return run_patch(d, ws, x, w, nullptr, nullptr, s, false, PROBE_LOADER);
+    }
     const Geometry& g = d->g;
     // the x the microkernel reads: the internal copy when the layouts differ (made by the last call)
     const bool x_nhwc = d->implicit_nhwc && !d->implicit_slice;
@@ -1471,6 +1861,12 @@ int conv2d_kernel_probe(conv2d_desc* d, const void* x, const void* w, const floa
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return CONV2D_E_HIP;
     if (dev != d->device) return CONV2D_E_UNSUPPORTED;
+    if (d->patch_ran) {
+        hipStream_t s = static_cast<hipStream_t>(stream);
+        CV_TRY(order_after_last(d, s));
+        Ws ws{d};
+        return run_patch(d, ws, x, w, bias, y, s, false, PROBE_KERNEL);
+    }
     const Geometry& g = d->g;
     // the x and y the microkernel reads and writes: the internal copies when the layouts differ
     const bool x_nhwc = d->implicit_nhwc && !d->implicit_slice;
@@ -1501,7 +1897,7 @@ int conv2d_breakdown(conv2d_desc* d, int algo, conv2d_breakdown_t* out) {
     out->calls[CONV2D_PH_PRE_ANALYSIS] = 1;
     if (algo == CONV2D_ALGO_IMPLICIT_GEMM)
         out->fused_mask = (1u << CONV2D_PH_IN_TILING) | (1u << CONV2D_PH_IN_PACKING) |
-                          (d->implicit.ksplit > 1 && !d->implicit_slice ? 0u : (1u << CONV2D_PH_IN_UNPACKING));
+                          ((d->patch_ran ? d->patch.ksplit > 1 : d->implicit.ksplit > 1 && !d->implicit_slice) ? 0u : (1u << CONV2D_PH_IN_UNPACKING));
     else if (algo == CONV2D_ALGO_IM2COL_GEMM || algo == CONV2D_ALGO_WINOGRAD)
         out->fused_mask = (1u << CONV2D_PH_IN_TILING);
     else
@@ -1541,6 +1937,7 @@ int conv2d_set_timing(conv2d_desc* d, int mode) {
 int conv2d_plan_query(const conv2d_desc* d, int algo, conv2d_plan_info* out) {
     if (!d || !out) return CONV2D_E_NULL;
     if (algo < 0 || algo >= CONV2D_ALGO_COUNT) return CONV2D_E_INVALID;
+    const bool patch = algo == CONV2D_ALGO_AUTO && auto_patch(d);
     if (algo == CONV2D_ALGO_AUTO) algo = d->auto_algo;
     std::memset(out, 0, sizeof(*out));
     const Geometry& g = d->g;
@@ -1555,7 +1952,18 @@ int conv2d_plan_query(const conv2d_desc* d, int algo, conv2d_plan_info* out) {
     if (algo == CONV2D_ALGO_DIRECT && d->direct_nhwc) out->needs_reorder = 0;
     out->op_class = (int32_t)d->opclass;
     out->chunks = 1;
-    if (algo == CONV2D_ALGO_IMPLICIT_GEMM) {
+    if (patch) {
+        out->needs_reorder = 0;
+        out->tile_m = kPatchShapes[d->patch.cfg].bm;
+        out->tile_n = kPatchShapes[d->patch.cfg].bn;
+        out->kernel = CONV2D_KERNEL_GEMM;
+        out->kred_pad = (int32_t)(d->patch.nch * 16 * d->patch.ks * g.R * g.S);
+        out->ksplit = d->patch.ksplit;
+        if (d->patch.ksplit > 1) out->workspace_bytes = d->patch.ksplit * g.G * g.Kg * g.P * 4;
+        out->tail_tiles = d->patch.tail_tiles;
+        out->tail_pieces = d->patch.tail_pieces;
+        if (d->patch.tail_tiles > 0) out->workspace_bytes = patch_tail_bytes(d->patch);
+    } else if (algo == CONV2D_ALGO_IMPLICIT_GEMM) {
         out->tile_m = d->implicit.bm;
         out->tile_n = d->implicit.bn;
         out->kernel = CONV2D_KERNEL_GEMM;

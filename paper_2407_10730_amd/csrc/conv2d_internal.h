@@ -259,6 +259,63 @@ SlicePlan slice_plan(int64_t Cg, int64_t R, int64_t S, int64_t Ho, int64_t Wo, i
                      int xdt, int nw, int64_t W = 0, int pw = 0, bool pk = false, bool db = false);
 hipError_t launch_slice(const SliceArgs& a, int xdt, int ydt, int nw, hipStream_t stream);
 
+// Patch convolution on MFMA (patch_conv.hip): per block BM output channels x BN consecutive
+// output pixels; the input patch under the pixels sits in LDS, CK = 16 * ks channels at a time.
+// Pixels are counted through columns [cb*TW, cb*TW + TW) of all output rows (column block cb,
+// row = n*Ho + ho).  Patch rows are virtual input rows: image n's rows start at n*HV, output row
+// ho at tap row r reads virtual row n*HV + ho*lsh + r*dh, which is input row v*ish - ph (in the
+// image); likewise columns with lsw, isw.  (A dimension with one tap has lsh = 1, ish = stride.)
+enum PatchCfg { PATCH_64x128 = 0, PATCH_64x256 = 1, PATCH_128x128 = 2, PATCH_32x256 = 3, PATCH_256x128 = 4,
+                PATCH_CFG_COUNT = 5 };
+static const TileShape kPatchShapes[PATCH_CFG_COUNT] = {{64, 128}, {64, 256}, {128, 128}, {32, 256}, {256, 128}};
+enum { PATCH_LD_ONE = 0, PATCH_LD_VEC = 1, PATCH_LD_PAIR = 2 };  // how the patch is loaded
+struct PatchArgs {
+    const void* x;
+    uint32_t x_bytes;
+    const void* wp;       // packed filters (launch_pack_filters)
+    uint32_t wp_bytes;
+    const void* w;        // filters as given [G*Kg][Cg][RS] (fp32: sums that are not finite)
+    uint32_t w_bytes;
+    const float* bias;    // may be NULL
+    void* y;
+    uint32_t y_bytes;
+    int32_t x_cs, x_hs, x_ws;  // element strides of x: channel, row, column
+    int64_t x_ns;              // ... image
+    int32_t G, Cg, Kg, H, W, Ho, Wo, HoWo, R, S, RS, sh, sw, ph, pw, dh, dw;
+    int32_t lsh, lsw, ish, isw, HV, PW, TW, ncb;
+    int32_t rows;              // N * Ho
+    int32_t nslots;            // patch pixels (capacity)
+    int32_t tiles_q, grid_m, mtiles;  // pixel tiles per column block, BM tiles, 32-row tiles
+    int32_t nch, ksplit, split_ch;    // chunks of CK channels; split sp takes [sp*split_ch, ...)
+    int32_t epi, y_es, ldc;    // EPI_*; bytes per y element; NHWC: K, dense: row pitch
+    int64_t c_sstride;         // dense: elements between splits
+    // tail split (as GemmArgs): pieces of tail_ch chunks
+    int32_t tail_tiles, tail_pieces, tail_ch;
+    float* tail_part;          // [tail_tiles][tail_pieces][BM*BN]
+    uint32_t* tail_count;      // [tail_tiles]
+    int32_t loader_only;       // pack probe: staging and filter loads only
+    int32_t ypair;             // bf16 NCHW y: pixels 2i, 2i + 1 of a tile are one aligned word of y
+    FastDiv fd_tw, fd_ho, fd_hv, fd_pw, fd_ns;  // by TW, Ho, HV, PW, patch units per 8 channels
+};
+struct PatchPlan {
+    bool ok = false;
+    int32_t np = 1, ks = 1;    // bf16 planes per value (3: fp32 tensors), 16-channel steps per chunk
+    int32_t cfg = 0, un = 4;   // PatchCfg; staging units per thread
+    bool pt = false;           // 1x1 filter
+    int32_t ld = 0;            // PATCH_LD_*
+    int32_t TW = 0, ncb = 1, HV = 0, PW = 0, nslots = 0, tiles_q = 0, nch = 0, ksplit = 1, split_ch = 0;
+    int32_t lsh = 1, lsw = 1, ish = 1, isw = 1;
+    int32_t tail_tiles = 0, tail_pieces = 0, tail_ch = 0;
+    int64_t wp_bytes = 0;
+};
+hipError_t launch_pack_filters(const void* w, uint32_t w_bytes, void* wp, uint32_t wp_bytes, int G, int Kg, int Cg,
+                               int RS, int np, int ks, hipStream_t s);
+int patch_threads(const PatchPlan& p);  // threads per block
+int patch_units(const PatchPlan& p);    // staging units per thread: 1x1 layers exactly, others at most
+int64_t patch_lds_bytes(const PatchPlan& p);
+void patch_wave_tile(const PatchPlan& p, int* tm, int* tn);  // 32-row and 32-pixel tiles per wave
+hipError_t launch_patch(const PatchArgs& a, const PatchPlan& p, hipStream_t s);
+
 // weight repack to tap-major order: w [K][C/g][R*S] -> wr [K][R*S][C/g].
 hipError_t launch_repack_tap_major(const void* w, void* wr, int64_t k, int64_t cg, int64_t rs, int elem_bytes,
                                    hipStream_t stream);

@@ -159,72 +159,6 @@ __device__ __forceinline__ BlockWork block_work(const GemmArgs& A, int ksplit, i
     return w;
 }
 
-// Tail split: store this piece's partial tile, count its arrival, and in the piece that
-// arrives last replace acc by the sum of all pieces of the tile in piece order (the same
-// result whatever the arrival order).  Returns false in the other pieces, which are done.
-// The pieces of a tile may run on different XCDs, whose L2 caches are not coherent with
-// each other.  The partials are therefore stored and loaded with the device-scope cache
-// policy (sc1: written through to, and read from, the point where all XCDs agree), and each
-// piece waits for its stores to complete before it counts itself; no fence is used, since
-// a device-scope fence writes back and invalidates the whole L2 of the XCD and costs every
-// other block on it its cached input.  The counter is an atomic, coherent device-wide.
-// Partial layout: 16-byte unit ((i*TN + j)*4 + q)*256 + t of the piece's BM x BN tile, through
-// buffer operations with a wave-uniform base (no per-lane address kept alive).
-template <int TM, int TN>
-__device__ __forceinline__ bool tail_reduce(const GemmArgs& A, f32x16 (&acc)[TM][TN], const BlockWork& w,
-                                            int t) {
-    constexpr uint32_t PIECE = TM * TN * 4 * 256 * 16;  // bytes of one partial tile
-    constexpr int SC1 = 1 << 4;                         // buffer cache policy bit: device scope
-    __shared__ int s_last;
-    const __amdgpu_buffer_rsrc_t rp =
-        make_rsrc(A.tail_part, (uint32_t)A.tail_tiles * (uint32_t)A.tail_pieces * PIECE);
-    const uint32_t tile_base = (uint32_t)w.tail_tile * (uint32_t)A.tail_pieces * PIECE;
-    const uint32_t lane_off = (uint32_t)t * 16u;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 v{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                __builtin_amdgcn_raw_buffer_store_b128(
-                    __builtin_bit_cast(u32x4, v), rp, lane_off,
-                    (int)(tile_base + (uint32_t)w.piece * PIECE + (uint32_t)((i * TN + j) * 4 + q) * 4096u), SC1);
-            }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the partial is complete device-wide
-    __syncthreads();
-    if (t == 0)
-        s_last = __hip_atomic_fetch_add(A.tail_count + w.tail_tile, 1u, __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(A.tail_pieces - 1);
-    __syncthreads();
-    if (!s_last) return false;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-#pragma unroll 1
-    for (int pc = 0; pc < A.tail_pieces; ++pc) {
-        const uint32_t base = tile_base + (uint32_t)pc * PIECE;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 v = __builtin_bit_cast(
-                        f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                   rp, lane_off, (int)(base + (uint32_t)((i * TN + j) * 4 + q) * 4096u), SC1));
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
-                }
-    }
-    // ready for the next launch
-    if (t == 0) __hip_atomic_store(A.tail_count + w.tail_tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
-}
-
 // ============================================================================ fp32
 // Block: 256 threads = 4 waves arranged WM x WN over a BM x BN tile; each wave
 // owns (BM/WM) x (BN/WN) = TM x TN MFMA 32x32x2 tiles.  BK reduction rows per
@@ -523,7 +457,7 @@ __global__ __launch_bounds__(256, (BM * BN <= 4096 && BK == 16 ? 7 : 1)) void ge
 
     if (A.loader_only) return;
     if constexpr (EPI != EPI_DENSE) {
-        if (wk.tail_tile >= 0 && !tail_reduce<TM, TN>(A, acc, wk, t)) return;
+        if (wk.tail_tile >= 0 && !tail_reduce<TM, TN, 256>(A.tail_part, A.tail_count, A.tail_tiles, A.tail_pieces, acc, wk.tail_tile, wk.piece, t)) return;
     }
     store_tile<TM, TN, EPI, TOut>(A, acc, gi, sp, m0 + wm0, p0 + wn0, lrow, lcol);
 }
@@ -934,7 +868,7 @@ __global__ __launch_bounds__(256, (BM * BN <= 4096 && BK == 32 ? 7 : 1)) void ge
 
     if (A.loader_only) return;
     if constexpr (EPI != EPI_DENSE) {
-        if (wk.tail_tile >= 0 && !tail_reduce<TM, TN>(A, acc, wk, t)) return;
+        if (wk.tail_tile >= 0 && !tail_reduce<TM, TN, 256>(A.tail_part, A.tail_count, A.tail_tiles, A.tail_pieces, acc, wk.tail_tile, wk.piece, t)) return;
     }
     store_tile<TM, TN, EPI, TOut>(A, acc, gi, sp, m0 + wm0, p0 + wn0, lrow, lcol);
 }

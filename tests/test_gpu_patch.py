@@ -1,0 +1,193 @@
+"""The patch convolution (AUTO's implicit kernel on an input patch in LDS) against the fp64 oracle.
+
+Every tile config is forced (CONV2D_PATCH_CFG) on shapes that sit on its edges: partial pixel,
+channel and row tiles, image borders inside a tile, column blocks, stride, dilation, odd rows (no
+pixel pairs), groups, the split reduction and the tail split.  Gates as everywhere: fp32 1e-5 and
+bf16 1e-2 per output; integer data is exact (small integers are exact in bf16, so their fp32 split
+has no remainder, and every partial sum is an integer below 2^24).
+"""
+import os
+
+import numpy as np
+import pytest
+
+import datagen
+import oracle
+from paper_2407_10730_amd import binding as B
+from paper_2407_10730_amd.runner import DeviceConv
+
+pytestmark = pytest.mark.gpu
+
+GATE = {"f32": 1e-5, "bf16": 1e-2}
+TILES = {0: (64, 128), 1: (64, 256), 2: (128, 128), 3: (32, 256), 4: (256, 128)}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B.load()
+    yield
+    torch.cuda.synchronize()
+
+
+def _shape(n, c, h, w, k, r, s, st=1, pd=None, dl=1, g=1, layout="nchw", seed=31):
+    pd = dl * (r - 1) // 2 if pd is None else pd
+    return datagen.ConvShape(n=n, c=c, h=h, w=w, k=k, r=r, s=s, stride=(st, st), pad=(pd, pd), dil=(dl, dl),
+                             groups=g, layout=layout, seed=seed)
+
+
+SHAPES = [
+    _shape(1, 8, 1, 1, 1, 1, 1),                       # one pixel, one row of the tile
+    _shape(2, 17, 9, 11, 33, 3, 3),                    # odd rows, partial chunk, partial row tile
+    _shape(3, 40, 7, 7, 70, 3, 3, layout="nhwc"),      # several images per tile, 16-byte loads
+    _shape(3, 33, 14, 14, 65, 3, 3),                   # even rows, odd padding (pairs shifted by one)
+    _shape(2, 24, 16, 18, 48, 3, 3, st=2, dl=2),
+    _shape(1, 16, 5, 130, 32, 5, 5, pd=0),             # one output row, wider than a tile
+    _shape(2, 32, 12, 12, 24, 7, 7, g=2),
+    _shape(4, 24, 10, 30, 48, 1, 1),
+    _shape(2, 24, 11, 13, 40, 1, 1, st=2),
+    _shape(2, 72, 10, 12, 130, 1, 1, layout="nhwc"),
+    _shape(2, 12, 9, 10, 20, 1, 3, pd=1),
+]
+
+
+def _run(monkeypatch, cs, mode, env, calls=1):
+    import torch
+    monkeypatch.setenv("CONV2D_PATCH", "1")
+    for k, v in env.items():
+        monkeypatch.setenv("CONV2D_PATCH_" + k, str(v))
+    print(f"\n[case] patch {cs} {env} {mode}", flush=True)
+    dc = DeviceConv(cs, mode)
+    try:
+        plan = dc.plan()
+        if plan.algo != B.CONV2D_ALGO_IMPLICIT_GEMM or (plan.tile_m, plan.tile_n) != TILES[env["CFG"]]:
+            pytest.skip("this tile's patch does not fit, or AUTO takes another family")
+        ys = []
+        for _ in range(calls):
+            dc.y.fill_(float("nan"))
+            dc.run()
+            torch.cuda.synchronize()
+            ys.append(dc.y.clone())
+        assert all(torch.equal(ys[0], y) for y in ys)
+        return dc.y_nchw(), (dc.x_host, dc.w_host, dc.b_host), plan
+    finally:
+        dc.close()
+
+
+def _check(monkeypatch, cs, mode, env, calls=1):
+    y, (x, w, b), plan = _run(monkeypatch, cs, mode, env, calls)
+    ref, a = oracle.conv2d(x, w, b if cs.has_bias else None, cs.stride, cs.pad, cs.dil, cs.groups)
+    if mode == "integer" and cs.y_dtype == "f32":
+        assert np.array_equal(y, ref)
+    else:
+        _, pt = oracle.normalised_errors(y, ref, a)
+        assert pt <= GATE[cs.x_dtype], pt
+    return plan
+
+
+@pytest.mark.parametrize("cfg", TILES)
+@pytest.mark.parametrize("dt", ["f32", "bf16", "bf16-f32"])
+@pytest.mark.parametrize("i", range(len(SHAPES)))
+def test_patch_tiles(monkeypatch, i, dt, cfg):
+    xd, yd = dt.split("-")[0], dt.split("-")[-1]
+    if xd == "f32" and cfg == 4:
+        pytest.skip("fp32 has no 256 x 128 tile")
+    cs = SHAPES[i].with_(x_dtype=xd, y_dtype=yd)
+    _check(monkeypatch, cs, "integer", {"CFG": cfg, "CB": 1 + i % 2})
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("env", [{"CFG": 0, "KSPLIT": 3}, {"CFG": 2, "KSPLIT": 5}, {"CFG": 1, "TAIL": 2},
+                                 {"CFG": 0, "TAIL": 4}, {"CFG": 3, "TAIL": 16}], ids=str)
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+def test_patch_splits(monkeypatch, dt, env, layout):
+    """Split reduction (partials added by the unpack) and tail split (added by a tile's last
+    piece), partial last chunk; the same bits on every call."""
+    cs = _shape(2, 200, 10, 12, 72, 3, 3, layout=layout).with_(x_dtype=dt, y_dtype=dt)
+    plan = _check(monkeypatch, cs, "random", env, calls=4)
+    assert (plan.ksplit > 1) == ("KSPLIT" in env) and (plan.tail_pieces > 1) == ("TAIL" in env)
+
+
+@pytest.mark.parametrize("r", [1, 3, 5])
+@pytest.mark.parametrize("split", [0, 2])
+def test_patch_f32_nonfinite_and_huge(monkeypatch, r, split):
+    """fp32 values whose three-way split is not finite (infinities, NaN, values past the largest
+    bf16) give what plain fp32 sums give; outputs without them keep the fp32 gate."""
+    import torch
+    cs = _shape(2, 40, 9, 10, 48, r, r)
+    monkeypatch.setenv("CONV2D_PATCH", "1")
+    monkeypatch.setenv("CONV2D_PATCH_TAIL", str(split))
+    x, w, b = datagen.make_inputs(cs, "random")
+    x, w = x.copy(), (w * 1e-3).astype(np.float32)
+    x[0, 3, 2, 2], x[0, 7, 6, 5], x[1, 1, 4, 4], x[1, 30, 8, 9] = np.inf, -np.inf, np.nan, 3.4e38
+    dc = DeviceConv(cs, inputs=(x, w, b))
+    try:
+        assert dc.plan().algo == B.CONV2D_ALGO_IMPLICIT_GEMM
+        dc.run()
+        torch.cuda.synchronize()
+        y = dc.y_nchw()
+    finally:
+        dc.close()
+    with np.errstate(all="ignore"):
+        ref, a = oracle.conv2d(x, w, b, cs.stride, cs.pad, cs.dil, cs.groups)
+    assert np.array_equal(np.isnan(y), np.isnan(ref))
+    inf = np.isinf(ref)
+    assert np.array_equal(y[inf], ref[inf])
+    ok = np.isfinite(ref)
+    assert ok.any() and inf.any() and np.isnan(ref).any()
+    assert np.max(np.abs(y[ok] - ref[ok]) / a[ok]) <= GATE["f32"]
+
+
+def test_patch_probes_and_noalloc(monkeypatch):
+    """After an AUTO call that ran the patch kernel the probes launch it, and the no-allocation
+    entry point gives the same bits."""
+    import torch
+    monkeypatch.setenv("CONV2D_PATCH", "1")
+    cs = _shape(2, 64, 14, 14, 64, 3, 3)
+    dc = DeviceConv(cs, "random")
+    try:
+        dc.run()
+        torch.cuda.synchronize()
+        y0 = dc.y.clone()
+        B.conv2d_pack_probe(dc.desc, dc.x, dc.w)
+        torch.cuda.synchronize()
+        assert torch.equal(dc.y, y0)
+        y1 = torch.full_like(y0, float("nan"))
+        B.conv2d_fwd_noalloc(dc.desc, dc.x, dc.w, dc.b, y1, B.CONV2D_ALGO_AUTO, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        assert torch.equal(y1, y0)
+        if dc.plan().ksplit <= 1:
+            dc.y.zero_()
+            B.conv2d_kernel_probe(dc.desc, dc.x, dc.w, dc.b, dc.y)
+            torch.cuda.synchronize()
+            assert torch.equal(dc.y, y0)
+    finally:
+        dc.close()
+
+
+def test_patch_needs_its_alignment(monkeypatch):
+    """An x that is not aligned for the plan's loads takes the tiled GEMM instead."""
+    import torch
+    monkeypatch.setenv("CONV2D_PATCH", "1")
+    for layout, dt in (("nhwc", "f32"), ("nchw", "bf16"), ("nhwc", "bf16")):
+        cs = _shape(2, 32, 10, 12, 32, 3, 3, layout=layout).with_(x_dtype=dt, y_dtype=dt)
+        dc = DeviceConv(cs, "integer")
+        try:
+            buf = torch.empty(dc.x.numel() + 1, dtype=dc.x.dtype, device=dc.x.device)
+            xs = buf[1:].view(dc.x.shape)
+            xs.copy_(dc.x)
+            dc.run()
+            torch.cuda.synchronize()
+            y0 = dc.y.clone()
+            dc.y.zero_()
+            try:
+                B.conv2d_fwd(dc.desc, xs, dc.w, dc.b, dc.y, B.CONV2D_ALGO_AUTO, torch.cuda.current_stream())
+            except B.Conv2dError as e:
+                assert e.status == B.CONV2D_E_UNSUPPORTED
+                continue
+            torch.cuda.synchronize()
+            assert torch.equal(dc.y, y0)
+        finally:
+            dc.close()
