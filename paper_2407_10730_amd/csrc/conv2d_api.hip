@@ -64,6 +64,7 @@ struct ExplicitPlan {
     int64_t chunks = 0;
     int64_t col_bytes = 0;       // per chunk
     int64_t c_bytes = 0;         // per chunk
+    PatchPlan patch;             // the GEMM on the patch kernel, where ok
     int status = CONV2D_OK;
 };
 
@@ -77,6 +78,7 @@ struct WinoPlan {
     int64_t tiles = 0, tc = 0, chunks = 0;
     int64_t u_bytes = 0, v_bytes = 0, m_bytes = 0;  // V and M per chunk
     GemmPlan gemm;
+    PatchPlan patch;  // the GEMMs on the patch kernel, where ok (fp32)
 };
 
 int64_t elem_size(int dt) { return dt == CONV2D_BF16 ? 2 : 4; }
@@ -697,6 +699,89 @@ void plan_patch(conv2d_desc* d) {
     if (need > cap && implicit_scratch_bytes(d) <= cap) d->patch.ok = false;
 }
 
+PatchArgs patch_args(const Geometry& g, const PatchPlan& p, const void* x, const void* w, const float* bias, void* y,
+                     void* wp);
+
+// The dense GEMMs of the explicit and Winograd paths, C[gi] = A[gi] (M x Kred) B[gi] (Kred x P), are
+// 1x1 convolutions of one image row of P pixels in G groups: the patch kernel runs them where its
+// price is below `below` of the GEMM kernel's (by the implicit models; both count launches of the
+// same few microseconds).  CONV2D_PATCH_DENSE = 0 / 1 forces the choice, a larger
+// number is `below` in per cent.
+Geometry dense_geometry(int64_t G, int64_t M, int64_t Kred, int64_t P, int xdt) {
+    Geometry q{};
+    q.N = 1; q.C = G * Kred; q.H = 1; q.W = P; q.K = G * M; q.R = q.S = 1; q.Ho = 1; q.Wo = P;
+    q.sh = q.sw = q.dh = q.dw = 1; q.G = (int32_t)G;
+    q.Cg = Kred; q.Kg = M; q.Kred = Kred; q.P = P;
+    q.layout = CONV2D_NCHW; q.xdt = xdt; q.ydt = CONV2D_F32;
+    q.x_elems = q.C * P; q.w_elems = q.K * Kred; q.y_elems = q.K * P;
+    return q;
+}
+
+// max_splits > 1: the reduction may be split, as the caller's unpack adds the splits' results anyway.
+// Measured on MI355X over 260 drawn layers (geometric mean over all, the ones that stay included):
+// explicit fp32 1.24x, explicit bf16 1.18x (the dense GEMM did not split its reduction), no layer
+// over 10 % slower; Winograd N32 256->256 28x28 fp32 127 -> 94 us, small layers stay on the GEMM.
+PatchPlan plan_dense_patch(const Geometry& q, const GemmPlan& gp, double below, int64_t max_splits = 1) {
+    PatchPlan best;
+    const int64_t mode = env_int64("CONV2D_PATCH_DENSE", -1);
+    if (mode == 0 || std::getenv("CONV2D_GEMM") || q.x_elems * elem_size(q.xdt) > kBufferLimit ||
+        q.w_elems * elem_size(q.xdt) > kBufferLimit || q.y_elems * 4 > kBufferLimit)
+        return best;
+    double cost = 1e300;
+    for (int cfg = 0; cfg < PATCH_CFG_COUNT; ++cfg) {
+        PatchPlan p;
+        if (!patch_candidate(q, cfg, 1, &p)) continue;
+        const int64_t tiles = (int64_t)p.tiles_q * ceil_div(q.Kg, kPatchShapes[cfg].bm) * q.G;
+        for (int64_t S = 1; S <= std::min<int64_t>(max_splits, p.nch) && (S == 1 || tiles * S <= 1024); S *= 2) {
+            p.split_ch = (int32_t)ceil_div(p.nch, S);
+            p.ksplit = (int32_t)ceil_div(p.nch, p.split_ch);
+            const double c = patch_cost_us(q, p) - (p.ksplit > 1 ? kPatchCost[p.np == 3 ? 3 : 1][PC_UNPACK] : 0.0);
+            if (q.G * p.ksplit <= 65535 && c < cost) {
+                cost = c;
+                best = p;
+            }
+        }
+    }
+    const double* k = kImplicitCost[q.xdt == CONV2D_F32 ? 1 : 4];
+    const double rounds = (double)ceil_div(ceil_div(q.Kg, gp.bm) * ceil_div(q.P, gp.bn) * q.G, 256);
+    const double gemm = k[0] + 1e-6 * gp.bm * gp.bn * q.Kred * (k[6] + k[7] * (rounds - 1)) + k[8] * (rounds - 1) +
+                        k[9] * 1e-6 * (q.x_elems * elem_size(q.xdt) + q.y_elems * 4);
+    if (mode > 1) below = 0.01 * (double)mode;
+    if (best.ok && mode != 1 && cost >= below * gemm) best.ok = false;
+    return best;
+}
+
+// Packed filters behind `at` bytes of a workspace slot.
+int64_t packed_end(int64_t at, const PatchPlan& p) { return p.ok ? ceil_div(at, 256) * 256 + p.wp_bytes : at; }
+
+// The Winograd GEMMs' plan (fp32; the bf16 ones read V transposed).
+void plan_wino_patch(conv2d_desc* d) {
+    const Geometry& g = d->g;
+    WinoPlan& p = d->wino;
+    if (!p.ok || g.xdt != CONV2D_F32) return;
+    p.patch = plan_dense_patch(dense_geometry(p.npos, g.K, g.C, p.tc, CONV2D_F32), p.gemm, 0.9);
+    const int64_t cap0 = CONV2D_NOALLOC_SCRATCH_BYTES - 4096;
+    const int64_t rest = 512 + p.v_bytes + p.m_bytes +
+                         (g.layout == CONV2D_NHWC ? 4 * (g.x_elems + g.y_elems) + 512 : 0);
+    if (p.u_bytes + rest <= cap0 && packed_end(p.u_bytes, p.patch) + rest > cap0) p.patch.ok = false;
+}
+
+// The plan for chunks of P columns, run on one of q.P.
+hipError_t launch_dense_patch(PatchPlan p, const Geometry& q, const void* b, const void* w, void* wp, void* c,
+                              hipStream_t s) {
+    p.TW = (int32_t)q.P;
+    p.tiles_q = (int32_t)ceil_div(q.P, kPatchShapes[p.cfg].bn);
+    if (!patch_aligned(p, b)) return hipErrorInvalidValue;
+    PatchArgs a = patch_args(q, p, b, w, nullptr, c, wp);
+    if (p.ksplit > 1) {
+        a.epi = EPI_DENSE;
+        a.ldc = (int32_t)q.P;
+        a.c_sstride = q.y_elems;
+        a.y_bytes = (uint32_t)(p.ksplit * q.y_elems * 4);
+    }
+    return launch_patch(a, p, s);
+}
+
 void plan_explicit(conv2d_desc* d) {
     const Geometry& g = d->g;
     ExplicitPlan& e = d->expl;
@@ -722,6 +807,21 @@ void plan_explicit(conv2d_desc* d) {
     e.col_bytes = rows * row_col;
     e.c_bytes = rows * row_c;
     e.gemm = choose_tile(g.Kg, rows * g.Wo, g.G, g.Kred, g.xdt, g.Cg, false, true);
+    // one chunk's result may be split in parts that the unpack adds (under the workspace limits).  The
+    // thresholds are the best of 0.7 .. 1.6 over 260 drawn layers: the implicit model prices this GEMM,
+    // which never splits, about 0.8 of what fp32 calls measure
+    const int64_t splits = e.chunks > 1 ? 1 : std::min(std::min(cap - e.col_bytes, kBufferLimit) / e.c_bytes, (int64_t)8);
+    e.patch = plan_dense_patch(dense_geometry(g.G, g.Kg, g.Kred, rows * g.Wo, g.xdt), e.gemm, g.xdt == CONV2D_F32 ? 1.2 : 0.75, splits);
+    // (every chunk's columns need the same loads; the last chunk may be shorter)
+    const int64_t last = (total_rows - (e.chunks - 1) * rows) * g.Wo;
+    if (e.patch.ok && e.patch.ld == PATCH_LD_PAIR && last % 2 != 0) e.patch.ok = false;
+    // what fits the no-allocation entry point's scratch keeps fitting it
+    const int64_t cap0 = CONV2D_NOALLOC_SCRATCH_BYTES - 4096, base = e.col_bytes + e.c_bytes;
+    const int64_t table = 256 + (int64_t)sizeof(KTabEntry) * ceil_div(g.Kred, KTAB_ALIGN) * KTAB_ALIGN;
+    const int64_t reorder = g.layout == CONV2D_NHWC ? g.x_elems * elem_size(g.xdt) + g.y_elems * elem_size(g.ydt) + 512 : 0;
+    const int64_t split_c = e.patch.ok ? (e.patch.ksplit - 1) * e.c_bytes : 0;
+    if (base + table + reorder <= cap0 && packed_end(base + split_c, e.patch) + table + reorder > cap0) e.patch.ok = false;
+    if (e.patch.ok) e.c_bytes += split_c;
 }
 
 // ------------------------------------------------------------------ events
@@ -1118,6 +1218,52 @@ int run_implicit(conv2d_desc* d, Ws& ws, const void* x, const void* w, const flo
     return sc.end();
 }
 
+// Launch arguments of plan p for the convolution g (unsplit).
+PatchArgs patch_args(const Geometry& g, const PatchPlan& p, const void* x, const void* w, const float* bias, void* y,
+                     void* wp) {
+    const int64_t es = elem_size(g.xdt);
+    const bool nhwc = g.layout == CONV2D_NHWC;
+    PatchArgs a{};
+    a.x = x;
+    a.x_bytes = (uint32_t)(g.x_elems * es);
+    a.wp = wp;
+    a.wp_bytes = (uint32_t)p.wp_bytes;
+    a.w = w;
+    a.w_bytes = (uint32_t)(g.w_elems * es);
+    a.bias = bias;
+    a.y = y;
+    a.y_bytes = (uint32_t)(g.y_elems * elem_size(g.ydt));
+    a.x_cs = (int32_t)(nhwc ? 1 : g.H * g.W);
+    a.x_hs = (int32_t)(nhwc ? g.W * g.C : g.W);
+    a.x_ws = (int32_t)(nhwc ? g.C : 1);
+    a.x_ns = g.C * g.H * g.W;
+    a.G = g.G; a.Cg = (int32_t)g.Cg; a.Kg = (int32_t)g.Kg;
+    a.H = (int32_t)g.H; a.W = (int32_t)g.W; a.Ho = (int32_t)g.Ho; a.Wo = (int32_t)g.Wo;
+    a.HoWo = (int32_t)(g.Ho * g.Wo);
+    a.R = (int32_t)g.R; a.S = (int32_t)g.S; a.RS = (int32_t)(g.R * g.S);
+    a.sh = g.sh; a.sw = g.sw; a.ph = g.ph; a.pw = g.pw; a.dh = g.dh; a.dw = g.dw;
+    a.lsh = p.lsh; a.lsw = p.lsw; a.ish = p.ish; a.isw = p.isw;
+    a.HV = p.HV; a.PW = p.PW; a.TW = p.TW; a.ncb = p.ncb;
+    a.rows = (int32_t)(g.N * g.Ho);
+    a.nslots = p.nslots;
+    a.tiles_q = p.tiles_q;
+    a.grid_m = (int32_t)ceil_div(g.Kg, kPatchShapes[p.cfg].bm);
+    a.mtiles = (int32_t)ceil_div(g.Kg, 32);
+    a.nch = p.nch;
+    a.ksplit = p.ksplit;
+    a.split_ch = p.split_ch;
+    a.epi = nhwc ? EPI_NHWC : EPI_NCHW;
+    a.y_es = (int32_t)elem_size(g.ydt);
+    a.ldc = (int32_t)g.K;
+    a.fd_tw = make_fastdiv((uint32_t)p.TW);
+    a.fd_ho = make_fastdiv((uint32_t)g.Ho);
+    a.fd_hv = make_fastdiv((uint32_t)std::max(p.HV, 1));
+    a.fd_pw = make_fastdiv((uint32_t)std::max(p.PW, 1));
+    a.fd_ns = make_fastdiv((uint32_t)(p.nslots / (p.ld == PATCH_LD_PAIR ? 2 : 1)));
+    a.ypair = !nhwc && g.Wo % 2 == 0 && p.TW % 2 == 0 && ((uintptr_t)y & 3) == 0;
+    return a;
+}
+
 // The patch convolution: filters packed as MFMA operands on every call (they may change between
 // calls), then one launch that reads x and writes y in the layout they have.
 int run_patch(conv2d_desc* d, Ws& ws, const void* x, const void* w, const float* bias, void* y, hipStream_t s, bool ph,
@@ -1150,45 +1296,8 @@ int run_patch(conv2d_desc* d, Ws& ws, const void* x, const void* w, const float*
                                    (int)(g.R * g.S), p.np, p.ks, s));
         CV_TRY(sc.end());
     }
-    PatchArgs a{};
-    a.x = x;
-    a.x_bytes = (uint32_t)(g.x_elems * es);
-    a.wp = wp;
-    a.wp_bytes = (uint32_t)p.wp_bytes;
-    a.w = w;
-    a.w_bytes = (uint32_t)(g.w_elems * es);
-    a.bias = g.has_bias ? bias : nullptr;
-    a.y = y;
-    a.y_bytes = (uint32_t)(g.y_elems * elem_size(g.ydt));
-    a.x_cs = (int32_t)(nhwc ? 1 : g.H * g.W);
-    a.x_hs = (int32_t)(nhwc ? g.W * g.C : g.W);
-    a.x_ws = (int32_t)(nhwc ? g.C : 1);
-    a.x_ns = g.C * g.H * g.W;
-    a.G = g.G; a.Cg = (int32_t)g.Cg; a.Kg = (int32_t)g.Kg;
-    a.H = (int32_t)g.H; a.W = (int32_t)g.W; a.Ho = (int32_t)g.Ho; a.Wo = (int32_t)g.Wo;
-    a.HoWo = (int32_t)(g.Ho * g.Wo);
-    a.R = (int32_t)g.R; a.S = (int32_t)g.S; a.RS = (int32_t)(g.R * g.S);
-    a.sh = g.sh; a.sw = g.sw; a.ph = g.ph; a.pw = g.pw; a.dh = g.dh; a.dw = g.dw;
-    a.lsh = p.lsh; a.lsw = p.lsw; a.ish = p.ish; a.isw = p.isw;
-    a.HV = p.HV; a.PW = p.PW; a.TW = p.TW; a.ncb = p.ncb;
-    a.rows = (int32_t)(g.N * g.Ho);
-    a.nslots = p.nslots;
-    a.tiles_q = p.tiles_q;
-    a.grid_m = (int32_t)ceil_div(g.Kg, kPatchShapes[p.cfg].bm);
-    a.mtiles = (int32_t)ceil_div(g.Kg, 32);
-    a.nch = p.nch;
-    a.ksplit = p.ksplit;
-    a.split_ch = p.split_ch;
-    a.epi = nhwc ? EPI_NHWC : EPI_NCHW;
-    a.y_es = (int32_t)elem_size(g.ydt);
-    a.ldc = (int32_t)g.K;
+    PatchArgs a = patch_args(g, p, x, w, g.has_bias ? bias : nullptr, y, wp);
     a.loader_only = probe == PROBE_LOADER ? 1 : 0;
-    a.fd_tw = make_fastdiv((uint32_t)p.TW);
-    a.fd_ho = make_fastdiv((uint32_t)g.Ho);
-    a.fd_hv = make_fastdiv((uint32_t)std::max(p.HV, 1));
-    a.fd_pw = make_fastdiv((uint32_t)std::max(p.PW, 1));
-    a.fd_ns = make_fastdiv((uint32_t)(p.nslots / (p.ld == PATCH_LD_PAIR ? 2 : 1)));
-    a.ypair = !nhwc && g.Wo % 2 == 0 && p.TW % 2 == 0 && ((uintptr_t)y & 3) == 0;
     char* partials = static_cast<char*>(wp) + part_at;
     if (p.ksplit > 1) {
         a.y = partials;
@@ -1239,7 +1348,8 @@ int run_winograd(conv2d_desc* d, Ws& ws, const void* x, const void* w, const flo
     if (!p.ok) return p.status;
     void* wu = nullptr;
     void* wvm = nullptr;
-    CV_TRY(ws.get(BUF_WU, p.u_bytes, &wu));
+    CV_TRY(ws.get(BUF_WU, packed_end(p.u_bytes, p.patch), &wu));
+    char* wp = static_cast<char*>(wu) + ceil_div(p.u_bytes, 256) * 256;  // U packed for the patch kernel
     CV_TRY(ws.get(BUF_WVM, p.v_bytes + p.m_bytes, &wvm));
     const bool bf = g.xdt == CONV2D_BF16;  // U and V bf16, V [16][tc][C] from NHWC x
     const int64_t es = elem_size(g.xdt);
@@ -1250,6 +1360,9 @@ int run_winograd(conv2d_desc* d, Ws& ws, const void* x, const void* w, const flo
         Scope sc(d, CONV2D_ALGO_WINOGRAD, CONV2D_PH_PRE_REORDER, s, ph);
         CV_TRY(sc.begin());
         CV_HIP(launch_wino_filter(w, wu, (int)g.K, (int)g.C, p.mt, g.xdt, s));
+        if (p.patch.ok)
+            CV_HIP(launch_pack_filters(wu, (uint32_t)p.u_bytes, wp, (uint32_t)p.patch.wp_bytes, p.npos, (int)g.K,
+                                       (int)g.C, 1, p.patch.np, p.patch.ks, s));
         CV_TRY(sc.end());
     }
     WinoArgs wa{};
@@ -1301,7 +1414,10 @@ int run_winograd(conv2d_desc* d, Ws& ws, const void* x, const void* w, const flo
             a.HoWo = (int32_t)(g.Ho * g.Wo);
             Scope sc(d, CONV2D_ALGO_WINOGRAD, CONV2D_PH_IN_MICROKERNEL, s, ph);
             CV_TRY(sc.begin());
-            CV_HIP(dispatch_gemm(gp, a, bf ? BSRC_DENSE_T : BSRC_DENSE, EPI_DENSE, g.xdt, CONV2D_F32, p.npos, s));
+            if (p.patch.ok)
+                CV_HIP(launch_dense_patch(p.patch, dense_geometry(p.npos, g.K, g.C, wa.tc, CONV2D_F32), v, wu, wp, m, s));
+            else
+                CV_HIP(dispatch_gemm(gp, a, bf ? BSRC_DENSE_T : BSRC_DENSE, EPI_DENSE, g.xdt, CONV2D_F32, p.npos, s));
             CV_TRY(sc.end());
         }
         {
@@ -1320,7 +1436,15 @@ int run_explicit(conv2d_desc* d, Ws& ws, const void* x, const void* w, const flo
     const ExplicitPlan& e = d->expl;
     if (e.status != CONV2D_OK) return e.status;
     void* wsb = nullptr;
-    CV_TRY(ws.get(BUF_WS, e.col_bytes + e.c_bytes, &wsb));
+    CV_TRY(ws.get(BUF_WS, packed_end(e.col_bytes + e.c_bytes, e.patch), &wsb));
+    char* wp = static_cast<char*>(wsb) + ceil_div(e.col_bytes + e.c_bytes, 256) * 256;  // packed filters
+    if (e.patch.ok) {
+        Scope sc(d, CONV2D_ALGO_IM2COL_GEMM, CONV2D_PH_PRE_REORDER, s, ph);
+        CV_TRY(sc.begin());
+        CV_HIP(launch_pack_filters(w, (uint32_t)(g.w_elems * elem_size(g.xdt)), wp, (uint32_t)e.patch.wp_bytes, g.G,
+                                   (int)g.Kg, (int)g.Kred, 1, e.patch.np, e.patch.ks, s));
+        CV_TRY(sc.end());
+    }
     const KTabEntry* ktab = nullptr;
     CV_TRY(ws.table(s, &ktab));
     char* col = static_cast<char*>(wsb);
@@ -1373,7 +1497,10 @@ int run_explicit(conv2d_desc* d, Ws& ws, const void* x, const void* w, const flo
             a.HoWo = (int32_t)(g.Ho * g.Wo);
             Scope sc(d, CONV2D_ALGO_IM2COL_GEMM, CONV2D_PH_IN_MICROKERNEL, s, ph);
             CV_TRY(sc.begin());
-            CV_HIP(dispatch_gemm(gp, a, BSRC_DENSE, EPI_DENSE, g.xdt, CONV2D_F32, (int)g.G, s));
+            if (e.patch.ok)
+                CV_HIP(launch_dense_patch(e.patch, dense_geometry(g.G, g.Kg, g.Kred, pc, g.xdt), col, w, wp, cbuf, s));
+            else
+                CV_HIP(dispatch_gemm(gp, a, BSRC_DENSE, EPI_DENSE, g.xdt, CONV2D_F32, (int)g.G, s));
             CV_TRY(sc.end());
         }
         {
@@ -1387,6 +1514,8 @@ int run_explicit(conv2d_desc* d, Ws& ws, const void* x, const void* w, const flo
             a.HoWo = (int32_t)(g.Ho * g.Wo);
             a.p_begin = p_begin;
             a.y_nstride = g.K * g.Ho * g.Wo;
+            a.splits = e.patch.ok ? e.patch.ksplit : 1;
+            a.split_stride = g.G * g.Kg * pc;
             Scope sc(d, CONV2D_ALGO_IM2COL_GEMM, CONV2D_PH_IN_UNPACKING, s, ph);
             CV_TRY(sc.begin());
             CV_HIP(launch_unpack(a, g.ydt, (int)g.G, s));
@@ -1704,6 +1833,7 @@ int conv2d_desc_create(const conv2d_params* params, conv2d_desc** out) {
     build_ktab(d);
     plan_explicit(d);
     plan_winograd(d);
+    plan_wino_patch(d);
     // Grouped layers with few channels per group sum on the vector ALUs (depthwise and the
     // grouped direct kernel): a short reduction and few output channels per group waste most of
     // an MFMA tile.  Measured crossover on MI355X: C/g <= 16 with K/g <= 32 runs faster there in

@@ -191,3 +191,50 @@ def test_patch_needs_its_alignment(monkeypatch):
             assert torch.equal(dc.y, y0)
         finally:
             dc.close()
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("chunked", [False, True])
+@pytest.mark.parametrize("cs,limit", [(_shape(2, 9, 13, 11, 70, 3, 3, st=2), "20000"),
+                                      (_shape(2, 48, 8, 10, 24, 5, 5, g=4), "160000"),
+                                      (_shape(1, 200, 6, 7, 130, 1, 1, layout="nhwc"), "20000")],
+                         ids=["s2", "g4", "nhwc"])
+def test_patch_dense_im2col(monkeypatch, cs, limit, chunked, dt):
+    """The explicit path's GEMM on the patch kernel: one chunk (its result split where the planner
+    splits it) and several chunks, the last one shorter."""
+    import torch
+    monkeypatch.setenv("CONV2D_PATCH_DENSE", "1")
+    if chunked:
+        monkeypatch.setenv("CONV2D_WORKSPACE_LIMIT_BYTES", limit)
+    dc = DeviceConv(cs.with_(x_dtype=dt, y_dtype="f32"), "integer")
+    try:
+        assert (dc.plan(B.CONV2D_ALGO_IM2COL_GEMM).chunks > 1) == chunked
+        dc.run(B.CONV2D_ALGO_IM2COL_GEMM)
+        torch.cuda.synchronize()
+        y = dc.y_nchw()
+    finally:
+        dc.close()
+    ref, _ = oracle.conv2d(dc.x_host, dc.w_host, dc.b_host, cs.stride, cs.pad, cs.dil, cs.groups)
+    assert np.array_equal(y, ref)
+
+
+@pytest.mark.parametrize("mt", ["2", "4"])
+@pytest.mark.parametrize("limit", [None, "300000"])
+def test_patch_dense_winograd(monkeypatch, mt, limit):
+    """The Winograd GEMMs on the patch kernel, one chunk of tiles and several."""
+    import torch
+    monkeypatch.setenv("CONV2D_PATCH_DENSE", "1")
+    monkeypatch.setenv("CONV2D_WINO_TILE", mt)
+    if limit:
+        monkeypatch.setenv("CONV2D_WORKSPACE_LIMIT_BYTES", limit)
+    cs = _shape(2, 40, 17, 15, 72, 3, 3)
+    dc = DeviceConv(cs, "random")
+    try:
+        assert (dc.plan(B.CONV2D_ALGO_WINOGRAD).chunks > 1) == (limit is not None)
+        dc.run(B.CONV2D_ALGO_WINOGRAD)
+        torch.cuda.synchronize()
+        y = dc.y_nchw()
+    finally:
+        dc.close()
+    ref, a = oracle.conv2d(dc.x_host, dc.w_host, dc.b_host, cs.stride, cs.pad, cs.dil, cs.groups)
+    assert oracle.normalised_errors(y, ref, a)[1] <= GATE["f32"]
