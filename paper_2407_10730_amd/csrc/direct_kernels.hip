@@ -1689,6 +1689,156 @@ __global__ __launch_bounds__(256) void dw_nhwc_kernel(DirectArgs A, const TX* __
     }
 }
 
+// ------------------------------------------------------------------ NHWC depthwise, streamed rows
+// 3x3 layers at stride 1 and dilation 1.  The kernel above loads (and in bf16 unpacks) every input
+// row three times and each row's filter again, and its column loop is unrolled for S <= DWN_SMAX.
+// Here a thread keeps the filter of its 4 channels in registers and walks down a band of output
+// rows: an input row is loaded once, DWS_AHEAD rows before it is summed, and feeds the R output
+// rows whose windows hold it.  The R output rows in progress take turns in as many accumulator
+// sets (row i of the walk starts output row i and finishes output row i - R + 1), so every index
+// is static in a loop body of R rows.  The products of an output are added in the same order as
+// above, so results are the same bit for bit.
+// Bound by HBM latency at 3 waves per SIMD (146 registers in bf16, 166 in fp32).  2 pixels a thread:
+// 4 take 214 to 240 registers, 2 waves per SIMD.  us per call (filter reorder of about 5 us
+// included), kernel above -> this one: N32 C256 56x56 bf16 40 -> 31 (2.6 -> 3.3 TB/s), 4 pixels 36;
+// fp32 58 -> 49 (4.2 TB/s); N32 C96 112x112 bf16 54 -> 43, fp32 82 -> 71; N32 C672 14x14 bf16
+// 12.7 -> 11.2; small layers, bound by their two launches, the same.
+// 5x5 filters stay above: their 100 filter and 80 sum registers leave one wave per SIMD (N32 C144
+// 56x56 bf16 37 -> 45 us, N32 C672 14x14 20 -> 36).
+constexpr int DWS_PX = 2;
+constexpr int DWS_AHEAD = 2;
+constexpr int DWS_R = 3;
+
+template <typename TX, typename TY>
+__global__ __launch_bounds__(256) void dw_nhwc_rows_kernel(DirectArgs A, const TX* __restrict__ wt, int64_t total,
+                                                          int nbands, int band) {
+    constexpr int R = DWS_R;
+    constexpr int COLS = DWS_PX + R - 1;
+    typedef uint32_t raw_t __attribute__((ext_vector_type(sizeof(TX))));  // 4 channels: 2 or 4 words
+    const int64_t idx = dwn_remap(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
+    if (idx >= total) return;
+    const int cq = A.C / 4;
+    const int wgroups = (A.Wo + DWS_PX - 1) / DWS_PX;
+    const int c0 = 4 * (int)(idx % cq);
+    int64_t t = idx / cq;
+    const int wo0 = (int)(t % wgroups) * DWS_PX;
+    t /= wgroups;
+    const int ho0 = (int)(t % nbands) * band;
+    const int n = (int)(t / nbands);
+    const int rows = min(band, A.Ho - ho0);
+    const f32x4 bias =
+        A.bias ? f32x4{A.bias[c0], A.bias[c0 + 1], A.bias[c0 + 2], A.bias[c0 + 3]} : f32x4{0, 0, 0, 0};
+    const __amdgpu_buffer_rsrc_t rx = dk_rsrc(A.x, A.x_bytes);
+    const __amdgpu_buffer_rsrc_t rw = dk_rsrc(wt, (uint32_t)(R * R * A.C * (int)sizeof(TX)));
+    f32x4 wv[R * R];
+#pragma unroll
+    for (int i = 0; i < R * R; ++i) {
+        f32x4 v[1];
+        dwn_load<TX, 4>(rw, true, (int64_t)i * A.C + c0, v);
+        wv[i] = v[0];
+    }
+    // byte offset of each column from the start of an input row, or past the tensor
+    uint32_t coff[COLS];
+#pragma unroll
+    for (int j = 0; j < COLS; ++j) {
+        const int wi = wo0 - A.pw + j;
+        coff[j] = (unsigned)wi < (unsigned)A.W ? (uint32_t)(wi * A.C + c0) * (uint32_t)sizeof(TX) : OOB_OFF;
+    }
+    const int hi0 = ho0 - A.ph;
+    const int walk = rows + R - 1;
+    raw_t raw[R][COLS];
+    auto load = [&](int i, raw_t(&v)[COLS]) {
+        const int hi = hi0 + i;
+        const bool ok = ((unsigned)hi < (unsigned)A.H) & (i < walk);
+        const uint32_t row = (uint32_t)(((int64_t)n * A.H + hi) * A.W * A.C) * (uint32_t)sizeof(TX);
+#pragma unroll
+        for (int j = 0; j < COLS; ++j) {
+            const uint32_t off = (ok & (coff[j] != OOB_OFF)) ? row + coff[j] : OOB_OFF;
+            if constexpr (sizeof(TX) == 4)
+                v[j] = __builtin_bit_cast(raw_t, __builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, 0));
+            else
+                v[j] = __builtin_bit_cast(raw_t, __builtin_amdgcn_raw_buffer_load_b64(rx, off, 0, 0));
+        }
+    };
+    f32x4 acc[R][DWS_PX];
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+#pragma unroll
+        for (int p = 0; p < DWS_PX; ++p) acc[k][p] = bias;
+#pragma unroll
+    for (int i = 0; i < DWS_AHEAD; ++i) load(i, raw[i]);
+    for (int i0 = 0; i0 < walk; i0 += R) {
+#pragma unroll
+        for (int ph = 0; ph < R; ++ph) {
+            load(i0 + ph + DWS_AHEAD, raw[(ph + DWS_AHEAD) % R]);
+            f32x4 xc[COLS];
+#pragma unroll
+            for (int j = 0; j < COLS; ++j) {
+                const raw_t h = raw[ph][j];
+                if constexpr (sizeof(TX) == 4)
+                    xc[j] = __builtin_bit_cast(f32x4, h);
+                else
+                    xc[j] = f32x4{__builtin_bit_cast(float, h[0] << 16), __builtin_bit_cast(float, h[0] & 0xFFFF0000u),
+                                  __builtin_bit_cast(float, h[1] << 16), __builtin_bit_cast(float, h[1] & 0xFFFF0000u)};
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int s = 0; s < R; ++s)
+#pragma unroll
+                    for (int p = 0; p < DWS_PX; ++p)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            acc[(ph - r + R) % R][p][e] =
+                                __builtin_fmaf(xc[p + s][e], wv[r * R + s][e], acc[(ph - r + R) % R][p][e]);
+            // the row that this input row finished
+            const int o = i0 + ph - R + 1;
+            f32x4(&a)[DWS_PX] = acc[(ph + 1) % R];
+            if ((unsigned)o < (unsigned)rows) {
+                const int64_t yb = (((int64_t)n * A.Ho + ho0 + o) * A.Wo + wo0) * A.K + c0;
+#pragma unroll
+                for (int p = 0; p < DWS_PX; ++p) {
+                    if (wo0 + p >= A.Wo) break;
+                    const int64_t e = yb + (int64_t)p * A.K;
+                    if constexpr (sizeof(TY) == 4) {
+                        *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(A.y) + e) = a[p];
+                    } else {
+                        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                        *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(A.y) + e) =
+                            u32x2{(uint32_t)dk_f32_to_bf16(a[p][0]) | ((uint32_t)dk_f32_to_bf16(a[p][1]) << 16),
+                                  (uint32_t)dk_f32_to_bf16(a[p][2]) | ((uint32_t)dk_f32_to_bf16(a[p][3]) << 16)};
+                    }
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < DWS_PX; ++p) a[p] = bias;
+        }
+    }
+}
+
+// Bands: as many as bring the launch to about 2048 waves (2 per SIMD); each band loads 2 halo rows
+// again.  1024 / 2048 / 4096 / 8192 waves ran N32 C256 56x56 bf16 in 29 / 31 / 34 / 35 us and N32 C96
+// 112x112 in 49 / 43 / 42 / 46 (fp32 83 / 71 / 69 / 69), N32 C672 14x14 bf16 in 10.6 / 11.2 / 13.2 /
+// 15.1: 2048 is the only one never slower than the kernel above.
+static void launch_dw_nhwc_rows(const DirectArgs& a, const void* wt, int xdt, int ydt, hipStream_t stream) {
+    const int64_t items = (int64_t)a.N * ((a.Wo + DWS_PX - 1) / DWS_PX) * (a.C / 4);
+    const int64_t target = 2048 * 64;
+    const int64_t want = std::min<int64_t>(std::max<int64_t>(1, (target + items - 1) / items), a.Ho);
+    const int band = (int)((a.Ho + want - 1) / want);
+    const int nbands = (a.Ho + band - 1) / band;
+    const int64_t total = items * nbands;
+    const dim3 grid((unsigned)((total + 255) / 256));
+    if (xdt == CONV2D_F32)
+        hipLaunchKernelGGL((dw_nhwc_rows_kernel<float, float>), grid, dim3(256), 0, stream, a, (const float*)wt,
+                           total, nbands, band);
+    else if (ydt == CONV2D_BF16)
+        hipLaunchKernelGGL((dw_nhwc_rows_kernel<uint16_t, uint16_t>), grid, dim3(256), 0, stream, a,
+                           (const uint16_t*)wt, total, nbands, band);
+    else
+        hipLaunchKernelGGL((dw_nhwc_rows_kernel<uint16_t, float>), grid, dim3(256), 0, stream, a,
+                           (const uint16_t*)wt, total, nbands, band);
+}
+
 bool dw_nhwc_supported(const DirectArgs& a) {
     return a.Cg == 1 && a.Kg == 1 && a.C == a.K && a.C % 4 == 0 && a.N > 0 && a.Ho > 0 && a.Wo > 0;
 }
@@ -1715,10 +1865,15 @@ static void launch_dw_nhwc_cfg(const DirectArgs& a, const void* wt, int xdt, int
 
 hipError_t launch_dw_nhwc(const DirectArgs& a, const void* wt, int xdt, int ydt, hipStream_t stream) {
     if (!dw_nhwc_supported(a)) return hipErrorInvalidValue;
-    // upper bound of the work items of every configuration (4 channels, 4 pixels per thread)
-    if ((int64_t)a.N * a.Ho * ((a.Wo + DWN_PX - 1) / DWN_PX) * (a.C / 4) > 0x7fffff00LL * 256)
+    // upper bound of the work items of every configuration (4 channels, 2 or 4 pixels per thread)
+    if ((int64_t)a.N * a.Ho * ((a.Wo + DWS_PX - 1) / DWS_PX) * (a.C / 4) > 0x7fffff00LL * 256)
         return hipErrorInvalidConfiguration;
     const bool s1 = a.sw == 1 && a.dw == 1 && a.S <= DWN_SMAX;
+    // 3x3 at stride 1: every input row loaded once
+    if (s1 && a.sh == 1 && a.dh == 1 && a.R == DWS_R && a.S == DWS_R) {
+        launch_dw_nhwc_rows(a, wt, xdt, ydt, stream);
+        return hipGetLastError();
+    }
     // bf16 with C a multiple of 8: 8 channels per thread, 16-byte loads
     const bool ch8 = xdt == CONV2D_BF16 && a.C % 8 == 0;
     if (s1 && ch8) launch_dw_nhwc_cfg<true, 8>(a, wt, xdt, ydt, stream);

@@ -910,6 +910,31 @@ def test_depthwise_nhwc(idx, dt):
     _check(cs.with_(y_dtype="f32"), DIRECT, "integer")
 
 
+# the 3x3 stride-1 kernel that streams rows (2 pixels x 4 channels a thread, bands of output rows):
+# one and two output rows (shorter than its 3-row cycle), odd Wo and Wo = 1, padding on one axis
+# only and wider than the filter, bands of 2 rows with a last one of 1, whole planes as one band
+# whose row count leaves each remainder of the cycle
+DW_NHWC_ROWS = [
+    _shape(1, 4, 1, 1, 4, 3, 3, pd=(1, 1), g=4, seed=270),
+    _shape(2, 12, 2, 7, 12, 3, 3, pd=(1, 1), g=12, seed=271, bias=False),
+    _shape(1, 8, 5, 3, 8, 3, 3, pd=(0, 0), g=8, seed=272),
+    _shape(1, 20, 6, 9, 20, 3, 3, pd=(0, 2), g=20, seed=273),
+    _shape(1, 8, 4, 5, 8, 3, 3, pd=(3, 4), g=8, seed=274),
+    _shape(2, 64, 101, 131, 64, 3, 3, pd=(1, 1), g=64, seed=275),
+    _shape(16, 512, 4, 128, 512, 3, 3, pd=(1, 1), g=512, seed=276),
+    _shape(16, 512, 5, 128, 512, 3, 3, pd=(1, 1), g=512, seed=277),
+    _shape(16, 512, 6, 128, 512, 3, 3, pd=(1, 1), g=512, seed=278),
+]
+
+
+@pytest.mark.parametrize("dt", [("f32", "f32"), ("bf16", "bf16"), ("bf16", "f32")], ids=lambda d: "-".join(d))
+@pytest.mark.parametrize("idx", range(len(DW_NHWC_ROWS)))
+def test_depthwise_nhwc_rows(idx, dt):
+    cs = DW_NHWC_ROWS[idx].with_(layout="nhwc", x_dtype=dt[0], y_dtype=dt[1])
+    _check(cs, DIRECT, "random")
+    _check(cs.with_(y_dtype="f32"), DIRECT, "integer")
+
+
 # split reductions with NHWC x and y: the unpack adds the partials and writes NHWC y (16- or
 # 8-byte stores of 4 channels when K/g is a multiple of 4), forced to 2, 3 and 5 splits
 @pytest.mark.parametrize("ksplit", ["2", "3", "5"])
