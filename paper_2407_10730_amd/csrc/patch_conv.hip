@@ -9,13 +9,18 @@
 // the patch needs barriers.
 //
 // Operands are bf16 in the matrix unit.  NP = 1: bf16 tensors.  NP = 3: fp32 tensors, every value
-// written as the sum of three bf16 values x = x0 + x1 + x2 (round to nearest, then the remainder
-// twice; 24 significand bits = 3 x 8, so the split is exact for normal values well above the
-// underflow range) and x*w summed from the six products of weight 2^-16 and more:
-// x2 w0 + x0 w2 + x1 w1 + x1 w0 + x0 w1 + x0 w0.  The three dropped products are below 2^-25 of
-// |x||w|, under the rounding of one fp32 addition, and the matrix unit does 16x the bf16 work of
-// its fp32 work per cycle, i.e. 2.7x through six products.  Relative error against float64 (2-norm) on
-// N32 64->64 56x56 3x3: 3.5e-7, against 4.2e-7 of the fp32 matrix instruction's sums.
+// times 2^24 written as the sum of three bf16 values x = x0 + x1 + x2 (round to nearest, then the
+// remainder twice) and x*w summed from the six products of weight 2^-16 and more:
+// x2 w0 + x0 w2 + x1 w1 + x1 w0 + x0 w1 + x0 w0.  24 significand bits = 3 x 8, so the split is
+// exact; the factor keeps the last bit of every fp32 value, subnormal ones included (2^-149),
+// above bf16's smallest normal number (without it x2 loses bits below |x| = 2^-110; it costs 0.6 %
+// of a call, 45.4 -> 45.6 us on N32 64->64 56x56 3x3).  The sums are multiplied by 2^-48 at the
+// end.  Where the scaled values overflow (an operand from 2^104, a sum from 2^80) or an operand is
+// not finite, the fp32 matrix instruction computes the tile instead.  The three dropped products
+// are together at most 2^-24 (1 + 2^-10) of |x||w| (|x1| <= 2^-8 |x|, |x2| <= 2^-17 |x|), about the
+// rounding of one fp32 addition; the matrix unit does 16x the bf16 work of its fp32 work per
+// cycle, i.e. 2.7x through six products.  Relative error against float64 (2-norm) on N32 64->64
+// 56x56 3x3: 3.6e-7, against 4.2e-7 of the fp32 matrix instruction's sums.
 //
 // Measured on MI355X, us per call (filter packing included), gather GEMM -> this kernel: N32 64->64
 // 56x56 3x3 fp32 70 -> 47 (107 -> 158 TFLOP/s), N32 256->512 56x56 1x1 stride 2 fp32 75 -> 67, N32
@@ -32,6 +37,9 @@
 namespace cv {
 
 namespace {
+
+// Factor of an fp32 operand before its split, and of the sum of products after it (see above).
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
 
 // Three bf16 planes of two fp32 values, packed (low half = lo).
 struct Split2 {
@@ -54,9 +62,10 @@ __device__ __forceinline__ Split2 split2(float lo, float hi) {
 // NP planes of 8 consecutive reduction values: planes[p] = 16 bytes of bf16.
 template <int NP>
 __device__ __forceinline__ void planes_of(const float (&f)[8], u32x4 (&planes)[NP]) {
+    constexpr float scale = NP == 3 ? kSplitScale : 1.0f;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const Split2 s = split2(f[2 * q], f[2 * q + 1]);
+        const Split2 s = split2(f[2 * q] * scale, f[2 * q + 1] * scale);
 #pragma unroll
         for (int p = 0; p < NP; ++p) planes[p][q] = s.p[p];
     }
@@ -441,9 +450,10 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void patch_conv_kernel(PatchArg
     }
 
     if constexpr (NP == 3) {
-        // A value that is not finite, or rounds past the largest bf16, splits into infinities of
-        // both signs; any such operand leaves a NaN in its sums.  A wave that finds one computes
-        // its tile again with the fp32 matrix instruction, whose result is the plain fp32 sum.
+        // A value that is not finite, or whose scaled form rounds past the largest bf16, splits into
+        // infinities of both signs; any such operand leaves a NaN in its sums, as a sum past the
+        // largest fp32 leaves an infinity.  A wave that finds one computes its tile again with the
+        // fp32 matrix instruction on the operands as they are: the plain fp32 sum.
         float z = 0.0f;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -477,6 +487,13 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void patch_conv_kernel(PatchArg
                         }
                     acc[i][j] = s;
                 }
+        } else {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[i][j][v] *= kSplitUnscale;
         }
     }
 

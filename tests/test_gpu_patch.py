@@ -140,6 +140,71 @@ def test_patch_f32_nonfinite_and_huge(monkeypatch, r, split):
     assert np.max(np.abs(y[ok] - ref[ok]) / a[ok]) <= GATE["f32"]
 
 
+def _dense_run(cs, inputs, algo):
+    import torch
+    dc = DeviceConv(cs, inputs=inputs)
+    try:
+        dc.run(algo)
+        torch.cuda.synchronize()
+        return dc.y_nchw()
+    finally:
+        dc.close()
+
+
+# powers of two of (x, w): plain values; values whose bf16 remainders would be subnormal or vanish
+# (below 2^-110), down to the smallest normal and below it; values whose scaled form overflows
+EXPONENTS = [(0, 0), (-108, 0), (-112, 0), (-126, 0), (-140, 0), (0, -112), (0, -126), (0, -140), (-60, -60),
+             (110, 0), (0, 110), (60, 60)]
+
+
+@pytest.mark.parametrize("e", EXPONENTS, ids=lambda e: f"x{e[0]}w{e[1]}")
+@pytest.mark.parametrize("algo", [B.CONV2D_ALGO_AUTO, B.CONV2D_ALGO_IM2COL_GEMM], ids=["auto", "im2col"])
+@pytest.mark.parametrize("r", [1, 3])
+@pytest.mark.parametrize("side", ["x", "w"])
+def test_patch_f32_keeps_every_bit(monkeypatch, side, r, algo, e):
+    """One operand holds 24 significant bits, the other is one-hot (a power of two, the rest zero), so
+    every output is one product of 24 bits: exact where it is a normal number, and it needs all three
+    planes of the split."""
+    monkeypatch.setenv("CONV2D_PATCH", "1")
+    monkeypatch.setenv("CONV2D_PATCH_DENSE", "1")
+    cs = _shape(2, 40, 9, 10, 48, r, r).with_(has_bias=False)
+    rng = np.random.default_rng(5)
+    odd = lambda shape: (1 + (2 * rng.integers(0, 1 << 22, shape) + 1) / 2.0 ** 23) * rng.choice([-1.0, 1.0], shape)
+    if side == "x":
+        x = odd((cs.n, cs.c, cs.h, cs.w))
+        w = np.zeros((cs.k, cs.c, r, r))
+        for k in range(cs.k):
+            w[k, (7 * k) % cs.c, k % r, (k // r) % r] = 1.0
+    else:
+        x = np.zeros((cs.n, cs.c, cs.h, cs.w))
+        for i in range(cs.n):  # windows of different ones do not overlap
+            for h in range(1, cs.h, 4):
+                for v in range(1, cs.w, 4):
+                    x[i, (5 * h + v + 11 * i) % cs.c, h, v] = 1.0
+        w = odd((cs.k, cs.c, r, r))
+    x, w = np.ldexp(x, e[0]).astype(np.float32), np.ldexp(w, e[1]).astype(np.float32)
+    y = _dense_run(cs, (x, w, np.zeros(cs.k, np.float32)), algo)
+    ref, _ = oracle.conv2d(x, w, None, cs.stride, cs.pad, cs.dil, cs.groups)
+    assert np.count_nonzero(ref) > 500
+    assert np.array_equal(y, ref.astype(np.float32))  # (a subnormal product rounds once)
+
+
+@pytest.mark.parametrize("scale", [(1e-33, 1.0), (1e-36, 1.0), (1.0, 1e-36), (1e-18, 1e-18)], ids=str)
+@pytest.mark.parametrize("algo", [B.CONV2D_ALGO_AUTO, B.CONV2D_ALGO_IM2COL_GEMM, B.CONV2D_ALGO_WINOGRAD],
+                         ids=["auto", "im2col", "winograd"])
+def test_patch_f32_small_magnitudes(monkeypatch, algo, scale):
+    """Tensors of small normal values keep the fp32 gate (each output is a normal number; its own
+    rounding there is below 2^-24)."""
+    monkeypatch.setenv("CONV2D_PATCH", "1")
+    monkeypatch.setenv("CONV2D_PATCH_DENSE", "1")
+    cs = _shape(2, 64, 14, 14, 64, 3, 3).with_(has_bias=False)
+    x, w, b = datagen.make_inputs(cs, "random")
+    x, w = (x * scale[0]).astype(np.float32), (w * scale[1]).astype(np.float32)
+    y = _dense_run(cs, (x, w, b), algo)
+    ref, a = oracle.conv2d(x, w, None, cs.stride, cs.pad, cs.dil, cs.groups)
+    assert np.max(np.abs(y - ref) / a) <= GATE["f32"]
+
+
 def test_patch_probes_and_noalloc(monkeypatch):
     """After an AUTO call that ran the patch kernel the probes launch it, and the no-allocation
     entry point gives the same bits."""
