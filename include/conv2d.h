@@ -60,7 +60,7 @@ enum { CONV2D_F32 = 0, CONV2D_BF16 = 1 };
 
 /* Algorithm families (ConvBench's main and baseline methods, Sec. III-C). */
 enum {
-    CONV2D_ALGO_AUTO = 0,          /* planner's choice */
+    CONV2D_ALGO_AUTO = 0,          /* planner's choice (see also CONV2D_KERNEL_PATCH) */
     CONV2D_ALGO_IMPLICIT_GEMM = 1, /* sliced direct convolution: im2col slices gathered into LDS, MFMA */
     CONV2D_ALGO_IM2COL_GEMM = 2,   /* explicit im2col pack, MFMA GEMM, unpack (ConvBench's default baseline) */
     CONV2D_ALGO_DIRECT = 3,        /* direct VALU kernels: depthwise (NCHW, or NHWC read and written
@@ -117,7 +117,8 @@ typedef struct {
  * summed GPU time (hipEvent) of phase p over `calls[p]` launches, except
  * PRE_ANALYSIS, which is the host time of conv2d_desc_create (calls = 1).
  * fused_mask has bit p set when phase p runs inside another phase's kernel
- * (its time is included there).  operation_ms is the sum of all phases
+ * (its time is included there); for IMPLICIT_GEMM, whose totals hold named and
+ * AUTO calls, IN_UNPACKING is set when no call of them launched an unpack.  operation_ms is the sum of all phases
  * (the timing tool's Operation Time); convolution_ms is the sum of the
  * in-convolution phases (its Convolution Time).  pack_is_preconv = 1 marks
  * that the explicit path's im2col is booked as IN_PACKING although the paper
@@ -139,8 +140,21 @@ typedef struct {
 /* Microkernels behind the algorithms.  IMPLICIT_GEMM runs either the tiled MFMA
  * GEMM that gathers im2col slices into LDS (GEMM) or, for short reductions
  * (C/g * R * S), the sliced direct kernel that keeps the input rows of a run of
- * output pixels in LDS and reads the columns from there (SLICE). */
-enum { CONV2D_KERNEL_GEMM = 0, CONV2D_KERNEL_SLICE = 1, CONV2D_KERNEL_DIRECT = 2 };
+ * output pixels in LDS and reads the columns from there (SLICE).
+ * The patch convolution (PATCH) packs the filters as MFMA operands, keeps the
+ * input patch under a tile of output pixels in LDS and applies every filter tap
+ * from there.  Where AUTO resolves to IMPLICIT_GEMM and the planner rates it
+ * faster, AUTO runs PATCH; a call that names CONV2D_ALGO_IMPLICIT_GEMM always runs
+ * GEMM or SLICE.  The plan of AUTO then has algo = IMPLICIT_GEMM and kernel =
+ * PATCH, and such calls are booked under IMPLICIT_GEMM.  PATCH reads NHWC x (and
+ * bf16 NCHW x of even width) in wider words: an AUTO call whose x is not aligned to
+ * 16 bytes (NHWC) or 4 bytes (bf16 NCHW) runs what IMPLICIT_GEMM runs, although
+ * the plan, which knows no addresses, says PATCH.  The two sum in another order, so
+ * their results differ by rounding.  The GEMMs of IM2COL_GEMM and fp32 WINOGRAD
+ * run on GEMM or on PATCH (as 1x1 convolutions of the packed matrices).
+ * PATCH multiplies fp32 tensors as three bf16 planes per value (every bit of the
+ * operands kept, six of the nine products, fp32 sums): fp32 accuracy. */
+enum { CONV2D_KERNEL_GEMM = 0, CONV2D_KERNEL_SLICE = 1, CONV2D_KERNEL_DIRECT = 2, CONV2D_KERNEL_PATCH = 3 };
 
 /* What the planner decided for one algorithm (for reports and tests). */
 typedef struct {
@@ -154,8 +168,9 @@ typedef struct {
                                  other layout than the kernel reads or writes) */
     int32_t op_class;         /* bit 0 pointwise, 1 grouped, 2 depthwise, 3 dilated, 4 rectangular, 5 strided */
     int32_t kernel;           /* microkernel that runs: CONV2D_KERNEL_* */
-    int32_t ksplit;           /* implicit GEMM: reduction split into this many parts (1 = none);
-                                 the parts' fp32 partial sums are added by the unpack phase.
+    int32_t ksplit;           /* implicit GEMM (and the explicit path's GEMM on PATCH): reduction
+                                 split into this many parts (1 = none); the parts' fp32 partial
+                                 sums are added by the unpack phase.
                                  DIRECT with K <= 4 (ungrouped, square 1/3/5/7 filter): the input
                                  channels' ranges of the few-output-channel kernel, likewise */
     int32_t tail_tiles;       /* implicit GEMM: output tiles computed in tail_pieces parts by extra
@@ -198,16 +213,17 @@ int conv2d_output_shape(const conv2d_desc* desc, int64_t out_nkhw[4]);
  * E_UNSUPPORTED (algo cannot run this op), E_ALLOC (explicit or Winograd
  * workspace over CONV2D_WORKSPACE_LIMIT_BYTES, default 1 GiB, even after chunking),
  * E_HIP (a launch failed).  Faults inside kernels surface at the next
- * synchronisation.  Results are bitwise reproducible for a fixed algo. */
+ * synchronisation.  Results are bitwise reproducible for a fixed algo (AUTO: and
+ * an x of the same alignment, see CONV2D_KERNEL_PATCH). */
 int conv2d_fwd(conv2d_desc* desc, const void* x, const void* w, const float* bias, void* y,
                int algo, void* stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): conv2d_fwd without any
  * allocation.  Same arguments, layouts, algorithms and results (bit for bit) as
- * conv2d_fwd; the workspaces (reordered copies, tap-major filters, split and
- * tail-split partial sums and counters, the tap table, the explicit path's
- * columns) come from one static device array of CONV2D_NOALLOC_SCRATCH_BYTES
+ * conv2d_fwd; the workspaces (reordered copies, tap-major or packed filters, split
+ * and tail-split partial sums and counters, the tap table, the explicit path's
+ * columns, Winograd's matrices) come from one static device array of CONV2D_NOALLOC_SCRATCH_BYTES
  * per GPU, which the library holds from its first use on that GPU until the
  * process ends.  The first call on a device looks the array up and clears its
  * counter region (queued on `stream`).  No events are recorded (the
@@ -230,15 +246,17 @@ int conv2d_fwd_noalloc(const conv2d_desc* desc, const void* x, const void* w, co
  * caller's events around the call, one kernel launch) over the full
  * microkernel's estimates the share of the packing fused into the implicit
  * algorithm.  x and w: the device pointers of a conv2d_fwd call; y and bias are
- * neither read nor written.  The probe reads the internal copies the last
- * implicit conv2d_fwd on this descriptor made (tap-major weights, a reordered
- * x), so it needs one such call first: E_NO_DATA otherwise.  E_NULL, E_UNSUPPORTED
+ * neither read nor written.  The probe launches the kernel of the last
+ * implicit conv2d_fwd on this descriptor (after an AUTO call that ran PATCH, that
+ * kernel) and reads the internal copies which that call made (tap-major or packed
+ * weights, a reordered x), so it needs one such call first: E_NO_DATA otherwise.  E_NULL, E_UNSUPPORTED
  * (no implicit algorithm for this shape, or another device), E_HIP. */
 int conv2d_pack_probe(conv2d_desc* desc, const void* x, const void* w, void* stream);
 
 /* Kernel probe (measurement of the microkernel's own duration, Sec. III-A's
  * microkernel step): queue only the implicit algorithm's microkernel launch --
- * the tiled MFMA GEMM with its fused gather and epilogue, or the sliced kernel --
+ * the tiled MFMA GEMM with its fused gather and epilogue, the sliced kernel, or
+ * the patch convolution, whichever the last implicit conv2d_fwd ran --
  * on `stream`, without the steps around it (filter repack, layout reorders, the
  * split reduction's unpack).  Back-to-back calls timed by the caller's events
  * give the kernel's average duration with no other launch in between.  x, w,
@@ -279,7 +297,8 @@ int conv2d_breakdown_reset(conv2d_desc* desc);
 /* Set the timing mode (CONV2D_TIMING_*).  Pending events are folded first. */
 int conv2d_set_timing(conv2d_desc* desc, int mode);
 
-/* Planner decisions for `algo` (AUTO: the algorithm AUTO resolves to). */
+/* Planner decisions for `algo` (AUTO: the algorithm AUTO resolves to, with the
+ * kernel that an AUTO call runs). */
 int conv2d_plan_query(const conv2d_desc* desc, int algo, conv2d_plan_info* out);
 
 /* Static text for a status code; never NULL. */

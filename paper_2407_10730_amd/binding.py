@@ -37,8 +37,9 @@ PHASE_NAMES = ["pre_analysis", "pre_reorder", "in_tiling", "in_packing", "in_mic
                "in_unpacking", "post_reorder"]
 CONV2D_PH_COUNT = 7
 CONV2D_TIMING_OFF, CONV2D_TIMING_TOTAL, CONV2D_TIMING_PHASES = 0, 1, 2
-CONV2D_KERNEL_GEMM, CONV2D_KERNEL_SLICE, CONV2D_KERNEL_DIRECT = 0, 1, 2
-KERNEL_NAMES = {CONV2D_KERNEL_GEMM: "gemm", CONV2D_KERNEL_SLICE: "slice", CONV2D_KERNEL_DIRECT: "direct"}
+CONV2D_KERNEL_GEMM, CONV2D_KERNEL_SLICE, CONV2D_KERNEL_DIRECT, CONV2D_KERNEL_PATCH = 0, 1, 2, 3
+KERNEL_NAMES = {CONV2D_KERNEL_GEMM: "gemm", CONV2D_KERNEL_SLICE: "slice", CONV2D_KERNEL_DIRECT: "direct",
+                CONV2D_KERNEL_PATCH: "patch"}
 
 # every function the header declares
 EXPORTS = ("conv2d_desc_create", "conv2d_desc_destroy", "conv2d_output_shape", "conv2d_fwd",

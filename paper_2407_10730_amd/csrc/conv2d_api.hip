@@ -36,6 +36,7 @@ struct PhaseAcc {
     double total_ms;
     int64_t total_calls;
     bool used;
+    bool unpacked;  // IMPLICIT_GEMM: a call launched an unpack kernel
 };
 
 struct EvRec {
@@ -1099,6 +1100,12 @@ int run_slice(conv2d_desc* d, const SlicePlan& sp, const Ws& ws, const void* x, 
     return sc.end();
 }
 
+// The implicit kernel of a call on x adds split partial sums in an unpack kernel.
+bool implicit_unpacks(const conv2d_desc* d, const void* x, bool patch) {
+    if (patch) return d->patch.ksplit > 1;
+    return d->implicit.ksplit > 1 && !(d->implicit_slice && slice_for(d, x));
+}
+
 // An NHWC y is written by the sliced kernel, or by the GEMM's own epilogue or the unpack of a
 // split reduction's partials when the GEMM gathers from NHWC x: no NCHW result, no
 // post-convolution reordering.
@@ -1608,6 +1615,14 @@ bool implicit_supported(const Geometry& g) {
 // AUTO runs the patch convolution.
 bool auto_patch(const conv2d_desc* d) { return d->auto_algo == CONV2D_ALGO_IMPLICIT_GEMM && d->patch.ok; }
 
+// The patch kernel's tile and padded reduction in a plan report.
+void report_patch(const PatchPlan& p, int64_t taps, conv2d_plan_info* out) {
+    out->kernel = CONV2D_KERNEL_PATCH;
+    out->tile_m = kPatchShapes[p.cfg].bm;
+    out->tile_n = kPatchShapes[p.cfg].bn;
+    out->kred_pad = (int32_t)(p.nch * 16 * p.ks * taps);
+}
+
 // Argument and algorithm checks shared by both forward entry points; resolves AUTO.
 // *patch: AUTO resolved to the patch convolution (booked as IMPLICIT_GEMM).
 int check_call(const conv2d_desc* d, const void* x, const void* w, const float* bias, const void* y, int* algo,
@@ -1933,6 +1948,7 @@ int conv2d_fwd(conv2d_desc* d, const void* x, const void* w, const float* bias, 
     if (algo == CONV2D_ALGO_IMPLICIT_GEMM) {
         d->implicit_ran = true;
         d->patch_ran = patch;
+        d->acc[algo].unpacked |= implicit_unpacks(d, x, patch);
     }
     return CONV2D_OK;
 }
@@ -2027,7 +2043,7 @@ int conv2d_breakdown(conv2d_desc* d, int algo, conv2d_breakdown_t* out) {
     out->calls[CONV2D_PH_PRE_ANALYSIS] = 1;
     if (algo == CONV2D_ALGO_IMPLICIT_GEMM)
         out->fused_mask = (1u << CONV2D_PH_IN_TILING) | (1u << CONV2D_PH_IN_PACKING) |
-                          ((d->patch_ran ? d->patch.ksplit > 1 : d->implicit.ksplit > 1 && !d->implicit_slice) ? 0u : (1u << CONV2D_PH_IN_UNPACKING));
+                          (a.unpacked ? 0u : (1u << CONV2D_PH_IN_UNPACKING));
     else if (algo == CONV2D_ALGO_IM2COL_GEMM || algo == CONV2D_ALGO_WINOGRAD)
         out->fused_mask = (1u << CONV2D_PH_IN_TILING);
     else
@@ -2084,10 +2100,7 @@ int conv2d_plan_query(const conv2d_desc* d, int algo, conv2d_plan_info* out) {
     out->chunks = 1;
     if (patch) {
         out->needs_reorder = 0;
-        out->tile_m = kPatchShapes[d->patch.cfg].bm;
-        out->tile_n = kPatchShapes[d->patch.cfg].bn;
-        out->kernel = CONV2D_KERNEL_GEMM;
-        out->kred_pad = (int32_t)(d->patch.nch * 16 * d->patch.ks * g.R * g.S);
+        report_patch(d->patch, g.R * g.S, out);
         out->ksplit = d->patch.ksplit;
         if (d->patch.ksplit > 1) out->workspace_bytes = d->patch.ksplit * g.G * g.Kg * g.P * 4;
         out->tail_tiles = d->patch.tail_tiles;
@@ -2117,6 +2130,10 @@ int conv2d_plan_query(const conv2d_desc* d, int algo, conv2d_plan_info* out) {
         out->tile_n = d->expl.gemm.bn;
         out->workspace_bytes = d->expl.col_bytes + d->expl.c_bytes;
         out->chunks = d->expl.chunks;
+        if (d->expl.patch.ok) {
+            report_patch(d->expl.patch, 1, out);
+            out->ksplit = d->expl.patch.ksplit;
+        }
         if (d->expl.status != CONV2D_OK) return d->expl.status;
     } else if (algo == CONV2D_ALGO_WINOGRAD) {
         out->tile_m = d->wino.gemm.bm;
@@ -2126,6 +2143,7 @@ int conv2d_plan_query(const conv2d_desc* d, int algo, conv2d_plan_info* out) {
         out->workspace_bytes = d->wino.u_bytes + d->wino.v_bytes + d->wino.m_bytes;
         out->chunks = d->wino.chunks;
         out->wino_tile = d->wino.mt;
+        if (d->wino.patch.ok) report_patch(d->wino.patch, 1, out);
         if (!d->wino.ok) return d->wino.status;
     } else {
         out->kernel = CONV2D_KERNEL_DIRECT;

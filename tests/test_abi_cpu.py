@@ -438,3 +438,38 @@ def test_smallk_direct_plan(monkeypatch):
     assert plan(bf).ksplit == 5
     monkeypatch.setenv("CONV2D_SMALLK", "0")
     assert plan(base).ksplit == 0
+
+
+def test_patch_kernel_has_its_own_identity(monkeypatch):
+    """The plan says where the patch convolution runs: in AUTO calls (resolved to IMPLICIT_GEMM)
+    and in the explicit and fp32 Winograd GEMMs; a named IMPLICIT_GEMM never runs it."""
+    for k in ("CONV2D_PATCH", "CONV2D_PATCH_DENSE", "CONV2D_GEMM", "CONV2D_SLICE"):
+        monkeypatch.delenv(k, raising=False)
+    cfg2 = datagen.CONFIGS["cfg2"]
+    assert cfg2.s == 3 and cfg2.c == 64
+
+    def plan(algo, cs=cfg2, **env):
+        for k, v in env.items():
+            monkeypatch.setenv(k, v)
+        d = B.conv2d_desc_create(params_for(cs))
+        for k in env:
+            monkeypatch.delenv(k)
+        try:
+            return B.conv2d_plan_query(d, algo)
+        finally:
+            B.conv2d_desc_destroy(d)
+
+    tiles = {(64, 128), (64, 256), (128, 128), (32, 256), (256, 128)}
+    p = plan(B.CONV2D_ALGO_AUTO)
+    assert (p.algo, p.kernel) == (B.CONV2D_ALGO_IMPLICIT_GEMM, B.CONV2D_KERNEL_PATCH)
+    assert (p.tile_m, p.tile_n) in tiles and p.kred_pad == 576
+    assert plan(B.CONV2D_ALGO_AUTO, CONV2D_PATCH="0").kernel == B.CONV2D_KERNEL_GEMM
+    for env in ({}, {"CONV2D_PATCH": "1"}):
+        assert plan(B.CONV2D_ALGO_IMPLICIT_GEMM, **env).kernel == B.CONV2D_KERNEL_GEMM
+    for algo, pad in ((B.CONV2D_ALGO_IM2COL_GEMM, 576), (B.CONV2D_ALGO_WINOGRAD, 64)):
+        p = plan(algo, CONV2D_PATCH_DENSE="1")
+        assert p.algo == algo and p.kernel == B.CONV2D_KERNEL_PATCH
+        assert (p.tile_m, p.tile_n) in tiles and p.kred_pad == pad
+        assert plan(algo, CONV2D_PATCH_DENSE="0").kernel == B.CONV2D_KERNEL_GEMM
+    bf = cfg2.with_(x_dtype="bf16", y_dtype="bf16")  # its Winograd GEMMs read V transposed
+    assert plan(B.CONV2D_ALGO_WINOGRAD, bf, CONV2D_PATCH_DENSE="1").kernel == B.CONV2D_KERNEL_GEMM

@@ -232,6 +232,30 @@ def test_patch_probes_and_noalloc(monkeypatch):
         dc.close()
 
 
+def test_patch_breakdown_does_not_depend_on_the_last_call(monkeypatch):
+    """IMPLICIT_GEMM's account holds named calls (here with an unpack) and AUTO's patch calls (without):
+    its totals and its fused phases are the same whichever ran last."""
+    import torch
+    monkeypatch.setenv("CONV2D_PATCH", "1")
+    monkeypatch.setenv("CONV2D_PATCH_KSPLIT", "1")
+    monkeypatch.setenv("CONV2D_KSPLIT", "2")
+    dc = DeviceConv(_shape(2, 64, 14, 14, 64, 3, 3), "random")
+    named = B.CONV2D_ALGO_IMPLICIT_GEMM
+    try:
+        assert dc.plan().kernel == B.CONV2D_KERNEL_PATCH and dc.plan().ksplit == 1
+        assert dc.plan(named).kernel == B.CONV2D_KERNEL_GEMM and dc.plan(named).ksplit == 2
+        for order in ((B.CONV2D_ALGO_AUTO,), (named, B.CONV2D_ALGO_AUTO), (B.CONV2D_ALGO_AUTO, named)):
+            B.conv2d_breakdown_reset(dc.desc)
+            for algo in order:
+                dc.run(algo)
+            torch.cuda.synchronize()
+            bd = dc.breakdown(named)
+            assert bd["fwd_calls"] == len(order)
+            assert ("in_unpacking" in bd["fused"]) == (named not in order)
+    finally:
+        dc.close()
+
+
 def test_patch_needs_its_alignment(monkeypatch):
     """An x that is not aligned for the plan's loads takes the tiled GEMM instead."""
     import torch
