@@ -450,10 +450,12 @@ void plan_winograd(conv2d_desc* d) {
 
 // Patch convolution (patch_conv.hip).  Every tile config, number of column blocks and split whose
 // patch fits LDS is priced by a linear model of its call, and the cheapest is taken; AUTO runs it
-// where that price is below 0.9 of the price of the implicit plan (a model of the same kind).  Both
-// were fitted on MI355X to measured calls of 2625 layers drawn over the whole range of sizes,
-// types and layouts (16 000 plans): median error 5-9 %, and the layers that the rule moves run
-// 1.62x as fast at the geometric mean, 1.7 % of all layers over 5 % slower than before.
+// where that price is below patch_margin of the price of the implicit plan (a model of the same
+// kind).  Both were fitted on MI355X to measured calls of 2625 layers drawn over the whole range of
+// sizes, types and layouts (16 000 plans): median error 5-9 %.  Over 31 819 other drawn layers the
+// rule moves 5944, which run 1.80x as fast at the geometric mean (0.43 of their time in all); 0.6 %
+// of the layers run over 5 % slower than on the implicit plan and 0.05 % over 20 %: mostly calls of
+// 10 to 20 us within the prices' errors, and wide layers of one or two channel chunks.
 // CONV2D_PATCH=0 switches the kernel off, 1 takes it wherever it can run; CONV2D_PATCH_CFG / _CB /
 // _KSPLIT / _TAIL force the tile, the column blocks, the split reduction and the pieces of the
 // tail split.
@@ -638,6 +640,29 @@ double patch_cost_us(const Geometry& g, const PatchPlan& p) {
            (q[PC_L] + (rounds - 1) * q[PC_RL]) * l + (q[PC_LN] + (rounds - 1) * q[PC_RLN]) * lines;
 }
 
+// The patch plan is taken below this share of the implicit plan's price: nearer the line the
+// errors of the two prices decide.  The classes below are those in which drawn layers between
+// their line and 0.9 ran no faster on average (0.94 - 1.04x) or lost as often as they won.
+double patch_margin(const conv2d_desc* d, double implicit_us) {
+    const Geometry& g = d->g;
+    const PatchPlan& p = d->patch;
+    const bool f32 = g.xdt == CONV2D_F32;
+    // no later chunk covers the first one's latency: up to three chunks of fp32 1x1 layers (0.97x),
+    // one chunk against the bf16 gather from NHWC x (1.04x); the sliced kernel's price is the
+    // least certain (1.00x)
+    if (d->implicit_slice || (f32 && p.pt && p.nch <= 3) || (!f32 && d->implicit_nhwc && p.nch == 1)) return 0.8;
+    // the fp32 gather from NHWC x reads whole lines, also at a stride (0.96x); parts of one chunk
+    // have nothing left to overlap (0.94x)
+    if (f32 && d->implicit_nhwc && p.ksplit > 1) {
+        if (p.split_ch == 1) return 0.6;
+        if (g.sh > 1 || g.sw > 1) return 0.8;
+    }
+    // short calls, where both prices are mostly fixed costs (1.0x; those on GEMM tiles of 32 rows,
+    // whose price is too low, gain 1.1x and more)
+    if (implicit_us < 35.0 && d->implicit.bm > 32) return 0.84;
+    return 0.9;
+}
+
 void plan_patch(conv2d_desc* d) {
     const Geometry& g = d->g;
     d->patch = PatchPlan{};
@@ -662,10 +687,13 @@ void plan_patch(conv2d_desc* d) {
             const TileShape ts = kPatchShapes[cfg];
             const int64_t tiles = (int64_t)p.tiles_q * ncb * ceil_div(g.Kg, ts.bm) * g.G;
             if (force_ks <= 1 && force_tail <= 0) consider(p);
-            // split reduction: whole chunks per split, about four blocks per CU at most
+            // split reduction: whole chunks per split, about four blocks per CU at most; up to four
+            // parts of a 1x1 layer, whose parts are short (N2 1344->64 11x11 fp32 NHWC in 21 parts
+            // took 30 us, the GEMM 16; 44 such layers of 5 and more parts ran 1.01x, 21 of them over
+            // 5 % slower)
             for (int64_t S = 2; S <= p.nch && force_tail <= 0; S = force_ks > 1 ? p.nch + 1 : 2 * S) {
                 const int64_t want = force_ks > 1 ? std::min<int64_t>(force_ks, p.nch) : S;
-                if (force_ks == 1 || want < 2 || (force_ks == 0 && tiles * want > 1024)) break;
+                if (force_ks == 1 || want < 2 || (force_ks == 0 && (tiles * want > 1024 || (p.pt && want > 4)))) break;
                 const int64_t per = ceil_div(p.nch, want), ks = ceil_div(p.nch, per);
                 if (g.G * ks > 65535 || ks * g.G * g.Kg * g.P * 4 > ((int64_t)256 << 20)) break;
                 PatchPlan v = p;
@@ -692,7 +720,8 @@ void plan_patch(conv2d_desc* d) {
         }
     }
     if (!d->patch.ok || mode > 0) return;
-    if (best >= 0.9 * implicit_cost_us(d)) d->patch.ok = false;
+    const double implicit = implicit_cost_us(d);
+    if (best >= patch_margin(d, implicit) * implicit) d->patch.ok = false;
     // the no-allocation entry point takes the same plan: keep what fits its scratch there
     const int64_t cap = CONV2D_NOALLOC_SCRATCH_BYTES - 4096;
     const int64_t need = ceil_div(d->patch.wp_bytes, 256) * 256 +
@@ -808,11 +837,15 @@ void plan_explicit(conv2d_desc* d) {
     e.col_bytes = rows * row_col;
     e.c_bytes = rows * row_c;
     e.gemm = choose_tile(g.Kg, rows * g.Wo, g.G, g.Kred, g.xdt, g.Cg, false, true);
-    // one chunk's result may be split in parts that the unpack adds (under the workspace limits).  The
-    // thresholds are the best of 0.7 .. 1.6 over 260 drawn layers: the implicit model prices this GEMM,
-    // which never splits, about 0.8 of what fp32 calls measure
+    // one chunk's result may be split in parts that the unpack adds (under the workspace limits).
+    // The line, as a share of the GEMM's price, which in fp32 reads about 0.8 of what its calls take:
+    // over 9277 drawn layers, of which 4000 ran the patch kernel below 1.2 (fp32) and 0.75 (bf16),
+    // those above the lines here gained nothing on average (fp32 groups of up to 16 output channels
+    // 0.97x, 75 of 147 over 5 % slower; fp32 layers of up to 64 above 1.05 1.03x; bf16 1.0x)
+    const bool few = g.G > 1 && g.Kg <= 16;
+    const double line = g.xdt == CONV2D_BF16 ? (few ? 0.6 : 0.7) : few ? 0.9 : g.Kg <= 64 ? 1.05 : 1.2;
     const int64_t splits = e.chunks > 1 ? 1 : std::min(std::min(cap - e.col_bytes, kBufferLimit) / e.c_bytes, (int64_t)8);
-    e.patch = plan_dense_patch(dense_geometry(g.G, g.Kg, g.Kred, rows * g.Wo, g.xdt), e.gemm, g.xdt == CONV2D_F32 ? 1.2 : 0.75, splits);
+    e.patch = plan_dense_patch(dense_geometry(g.G, g.Kg, g.Kred, rows * g.Wo, g.xdt), e.gemm, line, splits);
     // (every chunk's columns need the same loads; the last chunk may be shorter)
     const int64_t last = (total_rows - (e.chunks - 1) * rows) * g.Wo;
     if (e.patch.ok && e.patch.ld == PATCH_LD_PAIR && last % 2 != 0) e.patch.ok = false;

@@ -473,3 +473,47 @@ def test_patch_kernel_has_its_own_identity(monkeypatch):
         assert plan(algo, CONV2D_PATCH_DENSE="0").kernel == B.CONV2D_KERNEL_GEMM
     bf = cfg2.with_(x_dtype="bf16", y_dtype="bf16")  # its Winograd GEMMs read V transposed
     assert plan(B.CONV2D_ALGO_WINOGRAD, bf, CONV2D_PATCH_DENSE="1").kernel == B.CONV2D_KERNEL_GEMM
+
+
+# layers (n, c, h, w, k, r, s, stride, dilation, groups, layout, dtype) that measured 1.1 to 1.9x as long
+# on the patch kernel as on the plans they stay on
+STAYS = [
+    (2, 1344, 11, 11, 64, 1, 1, 1, 1, 1, "nhwc", "f32"),     # a 1x1 reduction in 21 parts
+    (8, 800, 25, 15, 64, 1, 1, 2, 1, 1, "nhwc", "f32"),      # 13 parts
+    (1, 48, 210, 210, 672, 1, 1, 1, 1, 1, "nchw", "f32"),    # two chunks of a 1x1 layer
+    (2, 32, 15, 15, 64, 3, 3, 2, 1, 1, "nhwc", "f32"),       # fp32 NHWC, parts of one chunk
+    (6, 8, 60, 60, 4, 3, 3, 1, 1, 1, "nchw", "bf16"),        # the sliced kernel's layers
+    (17, 16, 27, 27, 112, 5, 1, 2, 1, 1, "nchw", "bf16"),    # one chunk, NHWC gather
+]
+
+
+@pytest.mark.parametrize("case", STAYS, ids=lambda c: f"{c[1]}x{c[4]}-{c[5]}x{c[6]}-{c[10]}-{c[11]}")
+def test_patch_rule_leaves_slower_layers(monkeypatch, case):
+    for k in ("CONV2D_PATCH", "CONV2D_GEMM", "CONV2D_SLICE", "CONV2D_NHWC_GATHER"):
+        monkeypatch.delenv(k, raising=False)
+    n, c, h, w, k, r, s, st, dl, g, layout, dt = case
+    cs = datagen.ConvShape(n=n, c=c, h=h, w=w, k=k, r=r, s=s, stride=(st, st), pad=(dl * (r - 1) // 2,) * 2,
+                           dil=(dl, dl), groups=g, layout=layout, x_dtype=dt, y_dtype=dt, seed=1)
+    d = B.conv2d_desc_create(params_for(cs))
+    try:
+        p = B.conv2d_plan_query(d, B.CONV2D_ALGO_AUTO)
+    finally:
+        B.conv2d_desc_destroy(d)
+    assert p.algo == B.CONV2D_ALGO_IMPLICIT_GEMM and p.kernel != B.CONV2D_KERNEL_PATCH
+
+
+def test_explicit_small_groups_stay_on_the_gemm(monkeypatch):
+    """Groups of up to 16 output channels: these measured 1.11 to 1.15x as long with the explicit
+    path's GEMM on the patch kernel."""
+    for k in ("CONV2D_PATCH_DENSE", "CONV2D_GEMM", "CONV2D_WORKSPACE_LIMIT_BYTES"):
+        monkeypatch.delenv(k, raising=False)
+    for n, c, k, hw, r, st, dl, g, layout in ((1, 96, 320, 140, 5, 1, 2, 32, "nchw"), (15, 208, 208, 30, 7, 1, 1, 208, "nchw"),
+                                              (7, 160, 160, 103, 7, 2, 1, 160, "nhwc")):
+        cs = datagen.ConvShape(n=n, c=c, h=hw, w=hw, k=k, r=r, s=r, stride=(st, st), pad=(dl * (r // 2),) * 2,
+                               dil=(dl, dl), groups=g, layout=layout, seed=1)
+        d = B.conv2d_desc_create(params_for(cs))
+        try:
+            p = B.conv2d_plan_query(d, B.CONV2D_ALGO_IM2COL_GEMM)
+        finally:
+            B.conv2d_desc_destroy(d)
+        assert p.kernel == B.CONV2D_KERNEL_GEMM
