@@ -74,8 +74,10 @@ enum {
  * m = 2, 36 for m = 4), IN_UNPACKING the output transform with the bias (Sec. I
  * names the family; the minimal filtering algorithm is Lavin and Gray's).  The
  * planner picks the output tile m (conv2d_plan_info.wino_tile).  Its workspace
- * (transformed filters, then inputs and products per chunk of m x m output
- * tiles) obeys CONV2D_WORKSPACE_LIMIT_BYTES like the explicit path's. */
+ * beside the transformed filters (inputs and products of a chunk of m x m output
+ * tiles, packed filters where the GEMMs run on PATCH) obeys
+ * CONV2D_WORKSPACE_LIMIT_BYTES, like the explicit path's (columns and result of a
+ * chunk, packed filters). */
 
 /* Processing steps of the timing tool (Sec. III-A): pre-convolution analysis and
  * reordering; in-convolution tiling, packing, microkernel and unpacking;
@@ -161,8 +163,12 @@ typedef struct {
     int32_t algo;             /* resolved algorithm (never AUTO) */
     int32_t tile_m, tile_n;   /* GEMM block tile (output channels x output pixels); 0 for DIRECT */
     int32_t kred, kred_pad;   /* reduction length (C/g)*R*S and its padded length */
-    int64_t workspace_bytes;  /* device workspace this algorithm uses per chunk (explicit) or for the
-                                 partial sums of the split reduction or the tail split (implicit) */
+    int64_t workspace_bytes;  /* device workspace this algorithm uses per chunk (explicit; Winograd:
+                                 with the transformed filters) or for the partial sums of the split
+                                 reduction or the tail split (implicit).  Filter copies are not in
+                                 it: tap-major ones, and with kernel = PATCH the packed ones, 2 KiB
+                                 (fp32: 6 KiB) per 32 output channels and 32 values of the reduction,
+                                 rounded up, of each group (Winograd: of each position) */
     int64_t chunks;           /* explicit path: number of pack/GEMM/unpack chunks */
     int32_t needs_reorder;    /* 1 when a pre- or post-convolution layout reorder runs (x or y in the
                                  other layout than the kernel reads or writes) */

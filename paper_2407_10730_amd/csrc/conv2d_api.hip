@@ -95,6 +95,9 @@ int64_t env_int64(const char* name, int64_t dflt) {
     return (int64_t)v;
 }
 
+// Bytes that the explicit and Winograd paths' workspaces may take (see conv2d.h).
+int64_t workspace_limit() { return std::max<int64_t>(0, env_int64("CONV2D_WORKSPACE_LIMIT_BYTES", (int64_t)1 << 30)); }
+
 // Initial timing mode: OFF unless CONV2D_TIMING = total | phases (events cost every caller
 // time between kernels; the benchmark harness and the breakdown reports switch them on).
 int env_timing() {
@@ -418,9 +421,7 @@ void plan_winograd(conv2d_desc* d) {
     p.u_bytes = np * g.K * g.C * es;
     if (p.u_bytes > kBufferLimit) return;
     p.tiles = g.N * ceil_div(g.Ho, p.mt) * ceil_div(g.Wo, p.mt);
-    int64_t cap = env_int64("CONV2D_WORKSPACE_LIMIT_BYTES", (int64_t)1 << 30);
-    if (cap < 0) cap = 0;
-    int64_t tc = cap / (np * (g.C * es + g.K * 4));
+    int64_t tc = workspace_limit() / (np * (g.C * es + g.K * 4));
     tc = std::min<int64_t>(tc, kBufferLimit / (np * g.C * es));
     tc = std::min<int64_t>(tc, kBufferLimit / (np * g.K * 4));
     tc = std::min<int64_t>(tc, p.tiles);
@@ -781,6 +782,11 @@ PatchPlan plan_dense_patch(const Geometry& q, const GemmPlan& gp, double below, 
     return best;
 }
 
+// Bytes of packed filters of those GEMMs (32-row tiles, chunks of 32 channels, 1 or 3 planes).
+int64_t dense_packed_bytes(int64_t G, int64_t M, int64_t Kred, int xdt) {
+    return G * ceil_div(M, 32) * ceil_div(Kred, 32) * 2 * (xdt == CONV2D_F32 ? 3 : 1) * 1024;
+}
+
 // Packed filters behind `at` bytes of a workspace slot.
 int64_t packed_end(int64_t at, const PatchPlan& p) { return p.ok ? ceil_div(at, 256) * 256 + p.wp_bytes : at; }
 
@@ -789,11 +795,35 @@ void plan_wino_patch(conv2d_desc* d) {
     const Geometry& g = d->g;
     WinoPlan& p = d->wino;
     if (!p.ok || g.xdt != CONV2D_F32) return;
-    p.patch = plan_dense_patch(dense_geometry(p.npos, g.K, g.C, p.tc, CONV2D_F32), p.gemm, 0.9);
+    const int64_t all = p.tc;
+    const auto set_tiles = [&](int64_t tc) {
+        p.tc = tc;
+        p.chunks = ceil_div(p.tiles, tc);
+        p.v_bytes = p.npos * g.C * tc * 4;
+        p.m_bytes = p.npos * g.K * tc * 4;
+    };
+    const auto plan = [&]() { p.patch = plan_dense_patch(dense_geometry(p.npos, g.K, g.C, p.tc, CONV2D_F32), p.gemm, 0.9); };
+    plan();
+    // the packed filters count against the workspace limit, as on the explicit path
+    const int64_t wp = dense_packed_bytes(p.npos, g.K, g.C, CONV2D_F32) + 256, cap = workspace_limit();
+    if (p.patch.ok && p.v_bytes + p.m_bytes + wp > cap) {
+        const int64_t less = std::min(all, std::max<int64_t>(0, cap - wp) / (p.npos * (g.C + g.K) * 4));
+        const int64_t more = less < 1 ? 0 : ceil_div(p.tiles, less);
+        p.patch.ok = false;
+        if (less >= 1 && more <= p.chunks + std::max<int64_t>(1, p.chunks / 8)) {
+            set_tiles(less);
+            plan();
+            if (!p.patch.ok) set_tiles(all);
+        }
+    }
     const int64_t cap0 = CONV2D_NOALLOC_SCRATCH_BYTES - 4096;
     const int64_t rest = 512 + p.v_bytes + p.m_bytes +
                          (g.layout == CONV2D_NHWC ? 4 * (g.x_elems + g.y_elems) + 512 : 0);
-    if (p.u_bytes + rest <= cap0 && packed_end(p.u_bytes, p.patch) + rest > cap0) p.patch.ok = false;
+    // (768: as on the explicit path)
+    if (p.u_bytes + rest <= cap0 + 768 && packed_end(p.u_bytes, p.patch) + rest > cap0) {
+        p.patch.ok = false;
+        set_tiles(all);
+    }
 }
 
 // The plan for chunks of P columns, run on one of q.P.
@@ -818,13 +848,21 @@ void plan_explicit(conv2d_desc* d) {
     const int64_t xs = elem_size(g.xdt);
     const int64_t row_col = g.Wo * g.G * g.Kred * xs;  // col bytes of one output row (all groups)
     const int64_t row_c = g.Wo * g.G * g.Kg * 4;        // GEMM result bytes of one output row
-    int64_t cap = env_int64("CONV2D_WORKSPACE_LIMIT_BYTES", (int64_t)1 << 30);
-    if (cap < 0) cap = 0;
+    const int64_t cap = workspace_limit();
     const int64_t total_rows = g.N * g.Ho;
-    int64_t rows = cap / (row_col + row_c);
-    rows = std::min<int64_t>(rows, kBufferLimit / row_col);
-    rows = std::min<int64_t>(rows, kBufferLimit / row_c);
-    rows = std::min<int64_t>(rows, total_rows);
+    const auto rows_in = [&](int64_t bytes) {
+        int64_t rows = bytes / (row_col + row_c);
+        rows = std::min<int64_t>(rows, kBufferLimit / row_col);
+        rows = std::min<int64_t>(rows, kBufferLimit / row_c);
+        return std::min<int64_t>(rows, total_rows);
+    };
+    const auto set_rows = [&](int64_t rows) {
+        e.rows_per_chunk = rows;
+        e.chunks = ceil_div(total_rows, rows);
+        e.col_bytes = rows * row_col;
+        e.c_bytes = rows * row_c;
+    };
+    const int64_t rows = rows_in(cap);
     if (rows < 1) {
         e.status = CONV2D_E_ALLOC;
         e.rows_per_chunk = 0;
@@ -832,10 +870,7 @@ void plan_explicit(conv2d_desc* d) {
         return;
     }
     e.status = CONV2D_OK;
-    e.rows_per_chunk = rows;
-    e.chunks = ceil_div(total_rows, rows);
-    e.col_bytes = rows * row_col;
-    e.c_bytes = rows * row_c;
+    set_rows(rows);
     e.gemm = choose_tile(g.Kg, rows * g.Wo, g.G, g.Kred, g.xdt, g.Cg, false, true);
     // one chunk's result may be split in parts that the unpack adds (under the workspace limits).
     // The line, as a share of the GEMM's price, which in fp32 reads about 0.8 of what its calls take:
@@ -844,17 +879,37 @@ void plan_explicit(conv2d_desc* d) {
     // 0.97x, 75 of 147 over 5 % slower; fp32 layers of up to 64 above 1.05 1.03x; bf16 1.0x)
     const bool few = g.G > 1 && g.Kg <= 16;
     const double line = g.xdt == CONV2D_BF16 ? (few ? 0.6 : 0.7) : few ? 0.9 : g.Kg <= 64 ? 1.05 : 1.2;
-    const int64_t splits = e.chunks > 1 ? 1 : std::min(std::min(cap - e.col_bytes, kBufferLimit) / e.c_bytes, (int64_t)8);
-    e.patch = plan_dense_patch(dense_geometry(g.G, g.Kg, g.Kred, rows * g.Wo, g.xdt), e.gemm, line, splits);
-    // (every chunk's columns need the same loads; the last chunk may be shorter)
-    const int64_t last = (total_rows - (e.chunks - 1) * rows) * g.Wo;
-    if (e.patch.ok && e.patch.ld == PATCH_LD_PAIR && last % 2 != 0) e.patch.ok = false;
+    const int64_t wp = dense_packed_bytes(g.G, g.Kg, g.Kred, g.xdt) + 256;  // (aligned behind the rest)
+    const auto plan = [&]() {
+        const int64_t left = std::min(cap - wp - e.col_bytes, kBufferLimit);
+        const int64_t splits = e.chunks > 1 || left < e.c_bytes ? 1 : std::min(left / e.c_bytes, (int64_t)8);
+        e.patch = plan_dense_patch(dense_geometry(g.G, g.Kg, g.Kred, e.rows_per_chunk * g.Wo, g.xdt), e.gemm, line, splits);
+        // (every chunk's columns need the same loads; the last chunk may be shorter)
+        const int64_t last = (total_rows - (e.chunks - 1) * e.rows_per_chunk) * g.Wo;
+        if (e.patch.ok && e.patch.ld == PATCH_LD_PAIR && last % 2 != 0) e.patch.ok = false;
+    };
+    plan();
+    // the packed filters count against the workspace limit: smaller chunks, up to an eighth (at
+    // least one) more of them, or no patch kernel
+    if (e.patch.ok && e.col_bytes + e.c_bytes + wp > cap) {
+        const int64_t less = rows_in(cap - wp), more = less < 1 ? 0 : ceil_div(total_rows, less);
+        e.patch.ok = false;
+        if (less >= 1 && more <= e.chunks + std::max<int64_t>(1, e.chunks / 8)) {
+            set_rows(less);
+            plan();
+            if (!e.patch.ok) set_rows(rows);
+        }
+    }
     // what fits the no-allocation entry point's scratch keeps fitting it
     const int64_t cap0 = CONV2D_NOALLOC_SCRATCH_BYTES - 4096, base = e.col_bytes + e.c_bytes;
     const int64_t table = 256 + (int64_t)sizeof(KTabEntry) * ceil_div(g.Kred, KTAB_ALIGN) * KTAB_ALIGN;
     const int64_t reorder = g.layout == CONV2D_NHWC ? g.x_elems * elem_size(g.xdt) + g.y_elems * elem_size(g.ydt) + 512 : 0;
     const int64_t split_c = e.patch.ok ? (e.patch.ksplit - 1) * e.c_bytes : 0;
-    if (base + table + reorder <= cap0 && packed_end(base + split_c, e.patch) + table + reorder > cap0) e.patch.ok = false;
+    // (768: the most that the alignment allowed for above may exceed what the call takes)
+    if (base + table + reorder <= cap0 + 768 && packed_end(base + split_c, e.patch) + table + reorder > cap0) {
+        e.patch.ok = false;
+        set_rows(rows);
+    }
     if (e.patch.ok) e.c_bytes += split_c;
 }
 

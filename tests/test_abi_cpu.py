@@ -517,3 +517,66 @@ def test_explicit_small_groups_stay_on_the_gemm(monkeypatch):
         finally:
             B.conv2d_desc_destroy(d)
         assert p.kernel == B.CONV2D_KERNEL_GEMM
+
+
+def test_packed_filters_count_against_the_workspace_limit(monkeypatch):
+    """The explicit and Winograd GEMMs take the patch kernel only where its packed filters fit
+    CONV2D_WORKSPACE_LIMIT_BYTES beside a chunk."""
+    monkeypatch.setenv("CONV2D_PATCH_DENSE", "1")
+
+    def plan(cs, algo, limit):
+        monkeypatch.setenv("CONV2D_WORKSPACE_LIMIT_BYTES", str(limit))
+        d = B.conv2d_desc_create(params_for(cs))
+        try:
+            return B.conv2d_plan_query(d, algo)
+        finally:
+            B.conv2d_desc_destroy(d)
+
+    im2col, wino = B.CONV2D_ALGO_IM2COL_GEMM, B.CONV2D_ALGO_WINOGRAD
+    gemm, patch = B.CONV2D_KERNEL_GEMM, B.CONV2D_KERNEL_PATCH
+    base = datagen.ConvShape(n=1, c=200, h=6, w=7, k=130, r=1, s=1, stride=(1, 1), pad=(0, 0), dil=(1, 1), groups=1,
+                             seed=1)
+    packed = -(-130 // 32) * -(-200 // 32) * 6 * 1024
+    p = plan(base, im2col, 20000)
+    assert (p.kernel, p.chunks) == (gemm, 3) and p.workspace_bytes <= 20000
+    seen = set()
+    for extra in (0, 2048, 20000, 30000, 40000, 60000, 100000, 300000):
+        p = plan(base, im2col, packed + extra)
+        assert p.workspace_bytes + (packed if p.kernel == patch else 0) <= packed + extra
+        seen.add((p.kernel, p.chunks))
+    assert {(gemm, 1), (patch, 2), (patch, 1)} <= seen  # (a chunk more, or none where it fits)
+    big = datagen.ConvShape(n=4, c=1024, h=14, w=14, k=1024, r=3, s=3, stride=(1, 1), pad=(1, 1), dil=(1, 1), groups=1,
+                            seed=1)
+    packed = 32 * 288 * 6 * 1024
+    for limit, kernel in ((8 << 20, gemm), (packed - 1, gemm), (packed + (100 << 20), patch)):
+        p = plan(big.with_(n=16), im2col, limit)
+        assert p.kernel == kernel and p.workspace_bytes + (packed if kernel == patch else 0) <= limit
+    u, packed = 36 * 1024 * 1024 * 4, 36 * 32 * 32 * 6 * 1024
+    for limit, kernel in ((8 << 20, gemm), (packed, gemm), (packed + (12 << 20), patch), (1 << 30, patch)):
+        p = plan(big, wino, limit)
+        assert p.kernel == kernel and p.workspace_bytes - u + (packed if kernel == patch else 0) <= limit
+
+
+def test_explicit_at_the_edge_of_the_scratch_keeps_its_plan(monkeypatch):
+    """A layer whose columns, result and table end within the last 256 bytes of the no-allocation
+    scratch keeps the GEMM there: the patch kernel's packed filters would not fit behind them."""
+    monkeypatch.setenv("CONV2D_PATCH_DENSE", "1")
+    monkeypatch.delenv("CONV2D_WORKSPACE_LIMIT_BYTES", raising=False)
+    cap = B.CONV2D_NOALLOC_SCRATCH_BYTES - 4096
+    hits = 0
+    for k in range(1, 200):
+        for c in (16, 48, 64, 80, 112):
+            table = -(-c // 64) * 64 * 16  # 16-byte entries, 64 at a time
+            px = (cap - table - 256) // (4 * (c + k)) + 1  # columns of one row image
+            at = -(-4 * (c + k) * px // 256) * 256 + table
+            if not cap - 256 < at <= cap:
+                continue
+            cs = datagen.ConvShape(n=1, c=c, h=1, w=px, k=k, r=1, s=1, stride=(1, 1), pad=(0, 0), dil=(1, 1), groups=1,
+                                   seed=1)
+            d = B.conv2d_desc_create(params_for(cs))
+            try:
+                assert B.conv2d_plan_query(d, B.CONV2D_ALGO_IM2COL_GEMM).kernel == B.CONV2D_KERNEL_GEMM, (c, k, px)
+            finally:
+                B.conv2d_desc_destroy(d)
+            hits += 1
+    assert hits >= 3

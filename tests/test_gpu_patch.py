@@ -282,22 +282,32 @@ def test_patch_needs_its_alignment(monkeypatch):
             dc.close()
 
 
+def _packed(groups, m, kred, dt):
+    """Bytes of the packed filters of a dense GEMM."""
+    return groups * -(-m // 32) * -(-kred // 32) * (6 if dt == "f32" else 2) * 1024
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("chunked", [False, True])
-@pytest.mark.parametrize("cs,limit", [(_shape(2, 9, 13, 11, 70, 3, 3, st=2), "20000"),
-                                      (_shape(2, 48, 8, 10, 24, 5, 5, g=4), "160000"),
-                                      (_shape(1, 200, 6, 7, 130, 1, 1, layout="nhwc"), "20000")],
-                         ids=["s2", "g4", "nhwc"])
-def test_patch_dense_im2col(monkeypatch, cs, limit, chunked, dt):
+@pytest.mark.parametrize("cs", [_shape(2, 9, 13, 11, 70, 3, 3, st=2), _shape(2, 48, 8, 10, 24, 5, 5, g=4),
+                                _shape(1, 200, 6, 7, 130, 1, 1, layout="nhwc")], ids=["s2", "g4", "nhwc"])
+def test_patch_dense_im2col(monkeypatch, cs, chunked, dt):
     """The explicit path's GEMM on the patch kernel: one chunk (its result split where the planner
-    splits it) and several chunks, the last one shorter."""
+    splits it) and two chunks, the second one shorter, whose workspace and packed filters fill the
+    limit."""
     import torch
     monkeypatch.setenv("CONV2D_PATCH_DENSE", "1")
+    kred = cs.c // cs.groups * cs.r * cs.s
     if chunked:
-        monkeypatch.setenv("CONV2D_WORKSPACE_LIMIT_BYTES", limit)
+        ho = (cs.h + 2 * cs.pad[0] - cs.r) // cs.stride[0] + 1
+        wo = (cs.w + 2 * cs.pad[1] - cs.s) // cs.stride[1] + 1
+        row = wo * (cs.groups * kred * (4 if dt == "f32" else 2) + cs.k * 4)
+        limit = _packed(cs.groups, cs.k // cs.groups, kred, dt) + 256 + (cs.n * ho // 2 + 1) * row
+        monkeypatch.setenv("CONV2D_WORKSPACE_LIMIT_BYTES", str(limit))
     dc = DeviceConv(cs.with_(x_dtype=dt, y_dtype="f32"), "integer")
     try:
-        assert (dc.plan(B.CONV2D_ALGO_IM2COL_GEMM).chunks > 1) == chunked
+        plan = dc.plan(B.CONV2D_ALGO_IM2COL_GEMM)
+        assert plan.kernel == B.CONV2D_KERNEL_PATCH and plan.chunks == (2 if chunked else 1)
         dc.run(B.CONV2D_ALGO_IM2COL_GEMM)
         torch.cuda.synchronize()
         y = dc.y_nchw()
@@ -308,18 +318,22 @@ def test_patch_dense_im2col(monkeypatch, cs, limit, chunked, dt):
 
 
 @pytest.mark.parametrize("mt", ["2", "4"])
-@pytest.mark.parametrize("limit", [None, "300000"])
-def test_patch_dense_winograd(monkeypatch, mt, limit):
-    """The Winograd GEMMs on the patch kernel, one chunk of tiles and several."""
+@pytest.mark.parametrize("chunked", [False, True])
+def test_patch_dense_winograd(monkeypatch, mt, chunked):
+    """The Winograd GEMMs on the patch kernel, one chunk of tiles and two."""
     import torch
     monkeypatch.setenv("CONV2D_PATCH_DENSE", "1")
     monkeypatch.setenv("CONV2D_WINO_TILE", mt)
-    if limit:
-        monkeypatch.setenv("CONV2D_WORKSPACE_LIMIT_BYTES", limit)
     cs = _shape(2, 40, 17, 15, 72, 3, 3)
+    if chunked:
+        m = int(mt)
+        tiles, npos = 2 * -(-17 // m) * -(-15 // m), (m + 2) ** 2
+        limit = _packed(npos, 72, 40, "f32") + 256 + npos * (40 + 72) * 4 * (tiles * 3 // 5)
+        monkeypatch.setenv("CONV2D_WORKSPACE_LIMIT_BYTES", str(limit))
     dc = DeviceConv(cs, "random")
     try:
-        assert (dc.plan(B.CONV2D_ALGO_WINOGRAD).chunks > 1) == (limit is not None)
+        plan = dc.plan(B.CONV2D_ALGO_WINOGRAD)
+        assert plan.kernel == B.CONV2D_KERNEL_PATCH and plan.chunks == (2 if chunked else 1)
         dc.run(B.CONV2D_ALGO_WINOGRAD)
         torch.cuda.synchronize()
         y = dc.y_nchw()
