@@ -1,12 +1,13 @@
 """The patch convolution (AUTO's implicit kernel on an input patch in LDS) against the fp64 oracle.
 
+Every test checks in the plan that the patch kernel is what runs.
+
 Every tile config is forced (CONV2D_PATCH_CFG) on shapes that sit on its edges: partial pixel,
 channel and row tiles, image borders inside a tile, column blocks, stride, dilation, odd rows (no
 pixel pairs), groups, the split reduction and the tail split.  Gates as everywhere: fp32 1e-5 and
 bf16 1e-2 per output; integer data is exact (small integers are exact in bf16, so their fp32 split
 has no remainder, and every partial sum is an integer below 2^24).
 """
-import os
 
 import numpy as np
 import pytest
@@ -38,19 +39,34 @@ def _shape(n, c, h, w, k, r, s, st=1, pd=None, dl=1, g=1, layout="nchw", seed=31
                              groups=g, layout=layout, seed=seed)
 
 
+# (shape, column blocks)
 SHAPES = [
-    _shape(1, 8, 1, 1, 1, 1, 1),                       # one pixel, one row of the tile
-    _shape(2, 17, 9, 11, 33, 3, 3),                    # odd rows, partial chunk, partial row tile
-    _shape(3, 40, 7, 7, 70, 3, 3, layout="nhwc"),      # several images per tile, 16-byte loads
-    _shape(3, 33, 14, 14, 65, 3, 3),                   # even rows, odd padding (pairs shifted by one)
-    _shape(2, 24, 16, 18, 48, 3, 3, st=2, dl=2),
-    _shape(1, 16, 5, 130, 32, 5, 5, pd=0),             # one output row, wider than a tile
-    _shape(2, 32, 12, 12, 24, 7, 7, g=2),
-    _shape(4, 24, 10, 30, 48, 1, 1),
-    _shape(2, 24, 11, 13, 40, 1, 1, st=2),
-    _shape(2, 72, 10, 12, 130, 1, 1, layout="nhwc"),
-    _shape(2, 12, 9, 10, 20, 1, 3, pd=1),
+    (_shape(1, 8, 1, 1, 1, 1, 1), 1),                       # one pixel, one row of the tile
+    (_shape(2, 17, 9, 11, 33, 3, 3), 1),                    # odd rows, partial chunk, partial row tile
+    (_shape(2, 17, 9, 19, 33, 3, 3), 2),                    # ... in column blocks, the last one partial
+    (_shape(3, 40, 7, 7, 70, 3, 3, layout="nhwc"), 1),      # several images per tile, 16-byte loads
+    (_shape(3, 33, 14, 14, 65, 3, 3), 1),                   # even rows, odd padding (pairs shifted by one)
+    (_shape(3, 33, 14, 18, 65, 3, 3), 2),                   # ... and blocks of odd width
+    (_shape(2, 24, 16, 18, 48, 3, 3, st=2, dl=2), 1),
+    (_shape(1, 16, 5, 130, 32, 5, 5, pd=0), 2),             # one output row, wider than a tile
+    # groups: a partial last chunk beside the next group's channels, K/g a multiple of 4 and not
+    (_shape(2, 60, 12, 12, 40, 3, 3, g=2), 1),
+    (_shape(2, 60, 12, 12, 40, 3, 3, g=2, layout="nhwc"), 1),
+    (_shape(2, 66, 11, 26, 42, 3, 3, st=2, g=3), 1),
+    (_shape(2, 66, 11, 33, 42, 3, 3, st=2, g=3, layout="nhwc"), 2),
+    (_shape(2, 80, 9, 10, 48, 3, 3, g=2, layout="nhwc"), 1),
+    (_shape(1, 48, 12, 12, 70, 7, 7, g=2), 1),
+    (_shape(2, 72, 10, 12, 66, 1, 1, g=3, layout="nhwc"), 1),
+    (_shape(2, 72, 10, 12, 66, 1, 1, g=3), 1),
+    (_shape(4, 24, 10, 30, 48, 1, 1), 1),
+    (_shape(2, 24, 11, 13, 40, 1, 1, st=2), 1),
+    (_shape(2, 72, 10, 12, 130, 1, 1, layout="nhwc"), 1),
+    (_shape(2, 12, 9, 10, 20, 1, 3, pd=1), 1),
 ]
+# tiles whose patch needs more staging units than a block has
+UNFIT = {("f32", 6): {0, 3}, ("bf16", 6): {0, 4}, ("f32", 10): {0, 3}, ("bf16", 10): {0, 4}, ("bf16", 11): {0, 4}}
+TILE_CASES = [(i, dt, cfg) for i in range(len(SHAPES)) for dt in ("f32", "bf16", "bf16-f32") for cfg in TILES
+              if not (dt == "f32" and cfg == 4) and cfg not in UNFIT.get((dt.split("-")[0], i), ())]
 
 
 def _run(monkeypatch, cs, mode, env, calls=1):
@@ -62,8 +78,8 @@ def _run(monkeypatch, cs, mode, env, calls=1):
     dc = DeviceConv(cs, mode)
     try:
         plan = dc.plan()
-        if plan.algo != B.CONV2D_ALGO_IMPLICIT_GEMM or (plan.tile_m, plan.tile_n) != TILES[env["CFG"]]:
-            pytest.skip("this tile's patch does not fit, or AUTO takes another family")
+        assert plan.algo == B.CONV2D_ALGO_IMPLICIT_GEMM and plan.kernel == B.CONV2D_KERNEL_PATCH
+        assert (plan.tile_m, plan.tile_n) == TILES[env["CFG"]]
         ys = []
         for _ in range(calls):
             dc.y.fill_(float("nan"))
@@ -87,15 +103,38 @@ def _check(monkeypatch, cs, mode, env, calls=1):
     return plan
 
 
-@pytest.mark.parametrize("cfg", TILES)
-@pytest.mark.parametrize("dt", ["f32", "bf16", "bf16-f32"])
-@pytest.mark.parametrize("i", range(len(SHAPES)))
+@pytest.mark.parametrize("i,dt,cfg", TILE_CASES)
 def test_patch_tiles(monkeypatch, i, dt, cfg):
-    xd, yd = dt.split("-")[0], dt.split("-")[-1]
-    if xd == "f32" and cfg == 4:
-        pytest.skip("fp32 has no 256 x 128 tile")
-    cs = SHAPES[i].with_(x_dtype=xd, y_dtype=yd)
-    _check(monkeypatch, cs, "integer", {"CFG": cfg, "CB": 1 + i % 2})
+    cs, cb = SHAPES[i]
+    cs = cs.with_(x_dtype=dt.split("-")[0], y_dtype=dt.split("-")[-1])
+    _check(monkeypatch, cs, "integer", {"CFG": cfg, "CB": cb})
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("c,r", [(60, 3), (80, 3), (72, 1)])
+def test_patch_groups_do_not_meet(monkeypatch, layout, dt, c, r):
+    """A group whose input is all NaN or infinite leaves the other group's outputs as they are, its
+    partial last chunk included, and only its own outputs are not finite."""
+    import torch
+    monkeypatch.setenv("CONV2D_PATCH", "1")
+    cs = _shape(2, c, 9, 10, 48, r, r, g=2, layout=layout).with_(x_dtype=dt, y_dtype="f32")
+    x, w, b = datagen.make_inputs(cs, "integer")
+    x = x.copy()
+    x[0, c // 2:], x[1, c // 2:] = np.nan, np.inf
+    dc = DeviceConv(cs, "integer")
+    try:
+        assert dc.plan().kernel == B.CONV2D_KERNEL_PATCH
+        xt = torch.from_numpy(x if layout == "nchw" else np.ascontiguousarray(x.transpose(0, 2, 3, 1))).to(dc.x.dtype)
+        dc.x.copy_(xt)
+        dc.run()
+        torch.cuda.synchronize()
+        y = dc.y_nchw()
+    finally:
+        dc.close()
+    ref, _ = oracle.conv2d(np.nan_to_num(x, nan=0.0, posinf=0.0), w, b, cs.stride, cs.pad, cs.dil, cs.groups)
+    assert np.array_equal(y[:, :24], ref[:, :24])
+    assert not np.isfinite(y[0, 24:]).any()
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
@@ -124,7 +163,7 @@ def test_patch_f32_nonfinite_and_huge(monkeypatch, r, split):
     x[0, 3, 2, 2], x[0, 7, 6, 5], x[1, 1, 4, 4], x[1, 30, 8, 9] = np.inf, -np.inf, np.nan, 3.4e38
     dc = DeviceConv(cs, inputs=(x, w, b))
     try:
-        assert dc.plan().algo == B.CONV2D_ALGO_IMPLICIT_GEMM
+        assert dc.plan().kernel == B.CONV2D_KERNEL_PATCH
         dc.run()
         torch.cuda.synchronize()
         y = dc.y_nchw()
@@ -144,6 +183,7 @@ def _dense_run(cs, inputs, algo):
     import torch
     dc = DeviceConv(cs, inputs=inputs)
     try:
+        assert dc.plan(algo).kernel == B.CONV2D_KERNEL_PATCH
         dc.run(algo)
         torch.cuda.synchronize()
         return dc.y_nchw()
@@ -205,31 +245,63 @@ def test_patch_f32_small_magnitudes(monkeypatch, algo, scale):
     assert np.max(np.abs(y - ref) / a) <= GATE["f32"]
 
 
-def test_patch_probes_and_noalloc(monkeypatch):
-    """After an AUTO call that ran the patch kernel the probes launch it, and the no-allocation
-    entry point gives the same bits."""
+@pytest.mark.parametrize("env", [{"KSPLIT": 1, "TAIL": 0}, {"KSPLIT": 1, "TAIL": 2}, {"KSPLIT": 2}], ids=str)
+def test_patch_probes(monkeypatch, env):
+    """After an AUTO call that ran the patch kernel the probes launch it: the loader probe writes
+    nothing, the kernel probe the whole output (a split reduction's goes to its partials)."""
     import torch
     monkeypatch.setenv("CONV2D_PATCH", "1")
-    cs = _shape(2, 64, 14, 14, 64, 3, 3)
-    dc = DeviceConv(cs, "random")
+    for k, v in env.items():
+        monkeypatch.setenv("CONV2D_PATCH_" + k, str(v))
+    dc = DeviceConv(_shape(2, 64, 14, 14, 64, 3, 3), "random")
     try:
+        plan = dc.plan()
+        assert plan.kernel == B.CONV2D_KERNEL_PATCH and plan.ksplit == env["KSPLIT"]
+        assert (plan.tail_pieces > 1) == (env.get("TAIL") == 2)
         dc.run()
         torch.cuda.synchronize()
         y0 = dc.y.clone()
         B.conv2d_pack_probe(dc.desc, dc.x, dc.w)
         torch.cuda.synchronize()
         assert torch.equal(dc.y, y0)
-        y1 = torch.full_like(y0, float("nan"))
-        B.conv2d_fwd_noalloc(dc.desc, dc.x, dc.w, dc.b, y1, B.CONV2D_ALGO_AUTO, torch.cuda.current_stream())
-        torch.cuda.synchronize()
-        assert torch.equal(y1, y0)
-        if dc.plan().ksplit <= 1:
-            dc.y.zero_()
+        dc.y.zero_()
+        for _ in range(2):
             B.conv2d_kernel_probe(dc.desc, dc.x, dc.w, dc.b, dc.y)
-            torch.cuda.synchronize()
-            assert torch.equal(dc.y, y0)
+        torch.cuda.synchronize()
+        assert torch.equal(dc.y, y0) if plan.ksplit == 1 else not dc.y.any()
+        dc.run()  # (the tail split's counters are as the kernel left them)
+        torch.cuda.synchronize()
+        assert torch.equal(dc.y, y0)
     finally:
         dc.close()
+
+
+@pytest.mark.parametrize("env", [{"KSPLIT": 1, "TAIL": 0}, {"KSPLIT": 1, "TAIL": 2}, {"KSPLIT": 3}], ids=str)
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_patch_noalloc(monkeypatch, env, dt):
+    """The no-allocation entry point gives the same bits, also after a larger call used its scratch and,
+    with the tail split, its shared counters."""
+    import torch
+    monkeypatch.setenv("CONV2D_PATCH", "1")
+    for k, v in env.items():
+        monkeypatch.setenv("CONV2D_PATCH_" + k, str(v))
+    dcs = [DeviceConv(_shape(n, 96, 14, 14, 64, 3, 3).with_(x_dtype=dt, y_dtype=dt), "random") for n in (5, 2)]
+    try:
+        for dc in dcs:
+            plan = dc.plan()
+            assert plan.kernel == B.CONV2D_KERNEL_PATCH and plan.ksplit == env["KSPLIT"]
+            assert (plan.tail_pieces > 1) == (env.get("TAIL") == 2)
+            dc.run()
+        torch.cuda.synchronize()
+        s = torch.cuda.current_stream()
+        for dc in dcs + dcs[::-1] + dcs:
+            y = torch.full_like(dc.y, float("nan"))
+            B.conv2d_fwd_noalloc(dc.desc, dc.x, dc.w, dc.b, y, B.CONV2D_ALGO_AUTO, s)
+            torch.cuda.synchronize()
+            assert torch.equal(y, dc.y)
+    finally:
+        for dc in dcs:
+            dc.close()
 
 
 def test_patch_breakdown_does_not_depend_on_the_last_call(monkeypatch):
@@ -256,30 +328,30 @@ def test_patch_breakdown_does_not_depend_on_the_last_call(monkeypatch):
         dc.close()
 
 
-def test_patch_needs_its_alignment(monkeypatch):
-    """An x that is not aligned for the plan's loads takes the tiled GEMM instead."""
+@pytest.mark.parametrize("layout,dt", [("nhwc", "f32"), ("nchw", "bf16"), ("nhwc", "bf16")])
+def test_patch_needs_its_alignment(monkeypatch, layout, dt):
+    """An AUTO call whose x is not aligned for the plan's loads runs what a named IMPLICIT_GEMM runs."""
     import torch
     monkeypatch.setenv("CONV2D_PATCH", "1")
-    for layout, dt in (("nhwc", "f32"), ("nchw", "bf16"), ("nhwc", "bf16")):
-        cs = _shape(2, 32, 10, 12, 32, 3, 3, layout=layout).with_(x_dtype=dt, y_dtype=dt)
-        dc = DeviceConv(cs, "integer")
-        try:
-            buf = torch.empty(dc.x.numel() + 1, dtype=dc.x.dtype, device=dc.x.device)
-            xs = buf[1:].view(dc.x.shape)
-            xs.copy_(dc.x)
-            dc.run()
+    cs = _shape(2, 32, 10, 12, 32, 3, 3, layout=layout).with_(x_dtype=dt, y_dtype=dt)
+    dc = DeviceConv(cs, "random")
+    try:
+        assert dc.plan().kernel == B.CONV2D_KERNEL_PATCH
+        buf = torch.empty(dc.x.numel() + 1, dtype=dc.x.dtype, device=dc.x.device)
+        xs = buf[1:].view(dc.x.shape)
+        xs.copy_(dc.x)
+        ys = []
+        for algo in (B.CONV2D_ALGO_AUTO, B.CONV2D_ALGO_IMPLICIT_GEMM):
+            y = torch.full_like(dc.y, float("nan"))
+            B.conv2d_fwd(dc.desc, xs, dc.w, dc.b, y, algo, torch.cuda.current_stream())
             torch.cuda.synchronize()
-            y0 = dc.y.clone()
-            dc.y.zero_()
-            try:
-                B.conv2d_fwd(dc.desc, xs, dc.w, dc.b, dc.y, B.CONV2D_ALGO_AUTO, torch.cuda.current_stream())
-            except B.Conv2dError as e:
-                assert e.status == B.CONV2D_E_UNSUPPORTED
-                continue
-            torch.cuda.synchronize()
-            assert torch.equal(dc.y, y0)
-        finally:
-            dc.close()
+            ys.append(y)
+        assert torch.equal(ys[0], ys[1])
+        dc.y.copy_(ys[0])
+        ref, a = oracle.conv2d(dc.x_host, dc.w_host, dc.b_host, cs.stride, cs.pad, cs.dil, cs.groups)
+        assert oracle.normalised_errors(dc.y_nchw(), ref, a)[1] <= GATE[dt]
+    finally:
+        dc.close()
 
 
 def _packed(groups, m, kred, dt):
