@@ -463,17 +463,18 @@ void plan_winograd(conv2d_desc* d) {
 //
 // Microseconds per term: the launches (filter packing and kernel); a split reduction's unpack, and
 // per MB of its partials; per MB of one tile's tail-split partials, and the tail split; then for the
-// busiest CU's first block: matrix time at full rate, staging units per thread, chunks; the same
-// for each further block on that CU, and per such block; per MB of x and y; per MB of packed filters;
+// busiest CU's first block: matrix time at full rate, staging units per thread; the same for each
+// further block on that CU, and per such block; per MB of x and y; per MB of packed filters;
 // per 1000 KiB of filter operands loaded and of patch operands read from LDS by the first block, and by
-// each further one; per 1000 lines (128 bytes) of x under the block's patch, likewise.
-enum { PC_LAUNCH, PC_UNPACK, PC_PART, PC_TRED, PC_TAIL, PC_M, PC_U, PC_CH, PC_RM, PC_RU, PC_RCH, PC_R, PC_XY, PC_WP,
+// each further one; per 1000 lines (128 bytes) of x under the block's patch, likewise.  (The blocks
+// are dealt out to 256 CUs: a plan is made on the host, before it knows its device.)
+enum { PC_LAUNCH, PC_UNPACK, PC_PART, PC_TRED, PC_TAIL, PC_M, PC_U, PC_RM, PC_RU, PC_R, PC_XY, PC_WP,
        PC_A, PC_RA, PC_L, PC_RL, PC_LN, PC_RLN, PC_N };
 constexpr double kPatchCost[4][PC_N] = {
-    {8.82, 2.5, 0.302, 13.3, 1.89, 0.995, 0.0448, 0, 0, 0, 0, 1.7, 0.177, 1.38, 6.17, 1.93, 2.59, 4.24, 0.914, 0.671},  // bf16
-    {9.68, 2.41, 0.307, 16, 0, 1.3, 0, 0, 0, 0, 0, 0.802, 0.0709, 2.16, 0, 2.1, 2, 6.59, 2.95, 1.1},  // bf16, 1x1
-    {7.91, 2.05, 0.405, 11.6, 2.15, 1.26, 0.0737, 0, 1.09, 0.121, 0, 0.0265, 0.203, 0.849, 0, 0, 4.14, 0, 1.09, 0.397},  // fp32
-    {8.6, 1.82, 0.36, 16.5, 0.174, 1.7, 0.0431, 0, 0.559, 0, 0, 1.46, 0.0376, 0.896, 0, 0, 0, 0, 2.63, 1.86},  // fp32, 1x1
+    {8.82, 2.5, 0.302, 13.3, 1.89, 0.995, 0.0448, 0, 0, 1.7, 0.177, 1.38, 6.17, 1.93, 2.59, 4.24, 0.914, 0.671},  // bf16
+    {9.68, 2.41, 0.307, 16, 0, 1.3, 0, 0, 0, 0.802, 0.0709, 2.16, 0, 2.1, 2, 6.59, 2.95, 1.1},  // bf16, 1x1
+    {7.91, 2.05, 0.405, 11.6, 2.15, 1.26, 0.0737, 1.09, 0.121, 0.0265, 0.203, 0.849, 0, 0, 4.14, 0, 1.09, 0.397},  // fp32
+    {8.6, 1.82, 0.36, 16.5, 0.174, 1.7, 0.0431, 0.559, 0, 1.46, 0.0376, 0.896, 0, 0, 0, 0, 2.63, 1.86},  // fp32, 1x1
 };
 // The implicit plan's calls, by type and source of the GEMM's columns (tap table, tap-major, NHWC;
 // sliced kernel): launch, filter repack, layout reorder and per MB of it, split reduction's unpack
@@ -636,7 +637,7 @@ double patch_cost_us(const Geometry& g, const PatchPlan& p) {
     }
     return q[PC_LAUNCH] + (p.ksplit > 1 ? q[PC_UNPACK] + q[PC_PART] * 4e-6 * p.ksplit * g.G * g.Kg * g.P : 0) +
            (p.tail_tiles > 0 ? q[PC_TAIL] + q[PC_TRED] * 4e-6 * p.tail_pieces * ts.bm * ts.bn : 0) + q[PC_M] * m +
-           q[PC_U] * u + q[PC_CH] * ch + (rounds - 1) * (q[PC_RM] * m + q[PC_RU] * u + q[PC_RCH] * ch + q[PC_R]) +
+           q[PC_U] * u + (rounds - 1) * (q[PC_RM] * m + q[PC_RU] * u + q[PC_R]) +
            q[PC_XY] * xy + q[PC_WP] * 1e-6 * p.wp_bytes + (q[PC_A] + (rounds - 1) * q[PC_RA]) * a +
            (q[PC_L] + (rounds - 1) * q[PC_RL]) * l + (q[PC_LN] + (rounds - 1) * q[PC_RLN]) * lines;
 }
