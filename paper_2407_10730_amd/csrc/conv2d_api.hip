@@ -453,10 +453,11 @@ void plan_winograd(conv2d_desc* d) {
 // patch fits LDS is priced by a linear model of its call, and the cheapest is taken; AUTO runs it
 // where that price is below patch_margin of the price of the implicit plan (a model of the same
 // kind).  Both were fitted on MI355X to measured calls of 2625 layers drawn over the whole range of
-// sizes, types and layouts (16 000 plans): median error 5-9 %.  Over 31 819 other drawn layers the
-// rule moves 5944, which run 1.80x as fast at the geometric mean (0.43 of their time in all); 0.6 %
-// of the layers run over 5 % slower than on the implicit plan and 0.05 % over 20 %: mostly calls of
-// 10 to 20 us within the prices' errors, and wide layers of one or two channel chunks.
+// sizes, types and layouts (16 000 plans): median error 5-9 %.  Over 41 524 other drawn layers the
+// rule moves 8000, which run 1.75x as fast at the geometric mean (fp32 1.33x, bf16 2.02x; 0.44 of
+// their time in all); 0.9 % of the layers run over 5 % slower than on the implicit plan and 0.1 % over
+// 20 %, four in five of them bf16: calls of 10 to 20 us within the prices' errors, wide layers of one
+// or two channel chunks, 1x1 layers whose last, partial round of tiles is cut in two.
 // CONV2D_PATCH=0 switches the kernel off, 1 takes it wherever it can run; CONV2D_PATCH_CFG / _CB /
 // _KSPLIT / _TAIL force the tile, the column blocks, the split reduction and the pieces of the
 // tail split.
@@ -643,19 +644,19 @@ double patch_cost_us(const Geometry& g, const PatchPlan& p) {
 }
 
 // The patch plan is taken below this share of the implicit plan's price: nearer the line the
-// errors of the two prices decide.  The classes below are those in which drawn layers between
-// their line and 0.9 ran no faster on average (0.94 - 1.04x) or lost as often as they won.
+// errors of the two prices decide.  bf16 layers just below 0.9 win as often as they lose, in every
+// class that was looked at; the fp32 classes here are those in which drawn layers between their
+// line and 0.9 ran no faster on average (0.94 - 1.0x).
 double patch_margin(const conv2d_desc* d, double implicit_us) {
     const Geometry& g = d->g;
     const PatchPlan& p = d->patch;
-    const bool f32 = g.xdt == CONV2D_F32;
-    // no later chunk covers the first one's latency: up to three chunks of fp32 1x1 layers (0.97x),
-    // one chunk against the bf16 gather from NHWC x (1.04x); the sliced kernel's price is the
-    // least certain (1.00x)
-    if (d->implicit_slice || (f32 && p.pt && p.nch <= 3) || (!f32 && d->implicit_nhwc && p.nch == 1)) return 0.8;
-    // the fp32 gather from NHWC x reads whole lines, also at a stride (0.96x); parts of one chunk
-    // have nothing left to overlap (0.94x)
-    if (f32 && d->implicit_nhwc && p.ksplit > 1) {
+    if (g.xdt != CONV2D_F32) return 0.9;
+    // up to three chunks of a 1x1 layer: no later chunk covers the first one's latency (0.97x); the
+    // sliced kernel's price is the least certain (1.0x)
+    if (d->implicit_slice || (p.pt && p.nch <= 3)) return 0.8;
+    // the gather from NHWC x reads whole lines, also at a stride (0.96x); parts of one chunk have
+    // nothing left to overlap (0.94x)
+    if (d->implicit_nhwc && p.ksplit > 1) {
         if (p.split_ch == 1) return 0.6;
         if (g.sh > 1 || g.sw > 1) return 0.8;
     }
@@ -689,10 +690,9 @@ void plan_patch(conv2d_desc* d) {
             const TileShape ts = kPatchShapes[cfg];
             const int64_t tiles = (int64_t)p.tiles_q * ncb * ceil_div(g.Kg, ts.bm) * g.G;
             if (force_ks <= 1 && force_tail <= 0) consider(p);
-            // split reduction: whole chunks per split, about four blocks per CU at most; up to four
-            // parts of a 1x1 layer, whose parts are short (N2 1344->64 11x11 fp32 NHWC in 21 parts
-            // took 30 us, the GEMM 16; 44 such layers of 5 and more parts ran 1.01x, 21 of them over
-            // 5 % slower)
+            // split reduction: whole chunks per split, about four blocks per CU at most; up to 4 (fp32)
+            // or 16 (bf16) parts of a 1x1 layer, whose parts are short (N2 1344->64 11x11 fp32 NHWC in
+            // 21 parts took 30 us, the GEMM 16)
             for (int64_t S = 2; S <= p.nch && force_tail <= 0; S = force_ks > 1 ? p.nch + 1 : 2 * S) {
                 const int64_t want = force_ks > 1 ? std::min<int64_t>(force_ks, p.nch) : S;
                 if (force_ks == 1 || want < 2 || (force_ks == 0 && (tiles * want > 1024 || (p.pt && want > 4)))) break;
@@ -750,9 +750,10 @@ Geometry dense_geometry(int64_t G, int64_t M, int64_t Kred, int64_t P, int xdt) 
 }
 
 // max_splits > 1: the reduction may be split, as the caller's unpack adds the splits' results anyway.
-// Measured on MI355X over 260 drawn layers (geometric mean over all, the ones that stay included):
-// explicit fp32 1.24x, explicit bf16 1.18x (the dense GEMM did not split its reduction), no layer
-// over 10 % slower; Winograd N32 256->256 28x28 fp32 127 -> 94 us, small layers stay on the GEMM.
+// Measured on MI355X: of 7770 drawn explicit layers 3000 move, fp32 1.81x and bf16 1.90x as fast at the
+// geometric mean (the dense GEMM does not split its reduction), 0.7 % of all over 5 % slower, 6 layers over 10 %;
+// 1200 drawn Winograd layers run 1.14x as fast, one over 5 % slower; N32 256->256 28x28 fp32 130 -> 107 us.
+// Small layers stay on the GEMM.
 PatchPlan plan_dense_patch(const Geometry& q, const GemmPlan& gp, double below, int64_t max_splits = 1) {
     PatchPlan best;
     const int64_t mode = env_int64("CONV2D_PATCH_DENSE", -1);
@@ -1965,8 +1966,13 @@ int conv2d_desc_create(const conv2d_params* params, conv2d_desc** out) {
         d->auto_algo = CONV2D_ALGO_DIRECT;
     // 3x3 stride-1 fp32 layers with at least 128 input and output channels and output planes of
     // at least 8x8: Winograd F(4x4,3x3) does 4x fewer multiplications, which outweighs its
-    // transforms (measured 1.6-2.0x faster than the implicit GEMM for C, K = 128 .. 1024 on
-    // 14x14 to 112x112 planes on MI355X; 64 -> 64 channels on 56x56 gain under 10 %).  On 7x7
+    // transforms where there is enough work: N32 on 28x28 to 112x112 planes it takes 1/1.5 to 1/3.4 of
+    // the implicit GEMM's time for C = K = 128 .. 512, and against the patch convolution 1/1.08
+    // (128 channels), 1/1.6 (256) and 1/1.9 (512); 64 -> 64 channels run 1.25x as long as on that.
+    // Short calls lose, the more the more channels (transformed filters, small GEMMs): at batch 1
+    // on 14x14 planes 256 channels take 34 us and 1024 170 us, against 21 and 68 us on the
+    // patch convolution and 20 and 77 us on the GEMM; the line is even at N8 28x28 (128 -> 128: 34
+    // and 29 us, 256 -> 256: 56 and 59 us).  On 7x7
     // planes F(2x2,3x3) (2.25x fewer) pays off from about 4 GFLOP: 0.60-0.72x the time for N32
     // 512 -> 512, 256 -> 1024, 1024 -> 1024 and N8 2048 -> 2048, but 1.1x for N8 512 -> 512 and
     // 1.24x for N32 128 -> 128 (1.9 and 0.5 GFLOP), whose small per-position GEMMs stay inefficient.

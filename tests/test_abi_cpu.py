@@ -482,8 +482,8 @@ STAYS = [
     (8, 800, 25, 15, 64, 1, 1, 2, 1, 1, "nhwc", "f32"),      # 13 parts
     (1, 48, 210, 210, 672, 1, 1, 1, 1, 1, "nchw", "f32"),    # two chunks of a 1x1 layer
     (2, 32, 15, 15, 64, 3, 3, 2, 1, 1, "nhwc", "f32"),       # fp32 NHWC, parts of one chunk
-    (6, 8, 60, 60, 4, 3, 3, 1, 1, 1, "nchw", "bf16"),        # the sliced kernel's layers
-    (17, 16, 27, 27, 112, 5, 1, 2, 1, 1, "nchw", "bf16"),    # one chunk, NHWC gather
+    (10, 672, 8, 8, 128, 1, 1, 2, 1, 1, "nhwc", "f32"),      # 11 parts of a strided layer
+    (2, 32, 61, 16, 64, 3, 3, 2, 1, 1, "nhwc", "f32"),       # parts of one chunk, short call
 ]
 
 
