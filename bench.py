@@ -1,8 +1,9 @@
 """Benchmark of the conv2d forward primitive on one MI355X.
 
 Default workload: fp32 NCHW conv2d, N=32, C=K=64, 56x56, 3x3, stride 1, pad 1
-(the contraction-bound square-channel layer), AUTO algorithm (implicit GEMM).
-A step is one conv2d_fwd over the whole batch with inputs resident in HBM.
+(the contraction-bound square-channel layer), the algorithm AUTO resolves to,
+by its name (implicit GEMM).  Where an AUTO call itself runs the patch
+convolution in its place, "auto" gives that call's time.  A step is one conv2d_fwd over the whole batch with inputs resident in HBM.
 
 Prints ONE JSON line with the throughput (TFLOP/s), the dominant kernel's
 roofline position (its duration from the HIP events that enclose every phase
@@ -33,8 +34,9 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 _PLANNER = ["paper_2407_10730_amd/csrc/conv2d_api.hip", "paper_2407_10730_amd/csrc/conv2d_internal.h"]
 KERNEL_SOURCES = {
     "implicit_gemm": ["paper_2407_10730_amd/csrc/gemm_mfma.hip", "paper_2407_10730_amd/csrc/pack_kernels.hip",
-                      "paper_2407_10730_amd/csrc/slice_conv.hip"] + _PLANNER,
-    "im2col_gemm": ["paper_2407_10730_amd/csrc/gemm_mfma.hip", "paper_2407_10730_amd/csrc/pack_kernels.hip"] + _PLANNER,
+                      "paper_2407_10730_amd/csrc/slice_conv.hip", "paper_2407_10730_amd/csrc/device_common.h"] + _PLANNER,
+    "im2col_gemm": ["paper_2407_10730_amd/csrc/gemm_mfma.hip", "paper_2407_10730_amd/csrc/pack_kernels.hip",
+                    "paper_2407_10730_amd/csrc/patch_conv.hip", "paper_2407_10730_amd/csrc/device_common.h"] + _PLANNER,
     "direct": ["paper_2407_10730_amd/csrc/direct_kernels.hip"] + _PLANNER,
 }
 
@@ -215,6 +217,19 @@ def clock_ramp(dc, algo, seconds, torch):
     return {"seconds": time.perf_counter() - t0, "calls": calls}
 
 
+def auto_call(dc, algo, steps, warmup, flops, B, torch):
+    """The same steps through AUTO, where that runs another kernel than the algorithm it resolves
+    to does by its name (else None)."""
+    auto = dc.plan(B.CONV2D_ALGO_AUTO)
+    if auto.kernel == dc.plan(algo).kernel:
+        return None
+    wall, _, _ = time_algo(dc, B.CONV2D_ALGO_AUTO, steps, warmup, B, torch, B.CONV2D_TIMING_OFF)
+    ms = wall * 1e3 / steps
+    dc.run(algo)  # y and the probes' kernel back to the algorithm's
+    torch.cuda.synchronize()
+    return {"kernel": kernel_label(auto, B), "ms_per_step": ms, "tflops": flops / (ms * 1e-3) / 1e12}
+
+
 def launches_per_step(dc, algo, B, torch):
     """Kernel launches of one call (every phase launch once), from one PHASES-mode call."""
     B.conv2d_set_timing(dc.desc, B.CONV2D_TIMING_PHASES)
@@ -362,7 +377,7 @@ def summarize_profiles(d, workload, algo_name="implicit_gemm"):
             return list(csv.DictReader(f))
 
     def short(name):
-        return name.split("(")[0].replace("void ", "")[:90]
+        return name.replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "")[:90]
 
     lines = [f"# rocprofv3 summary: workload {workload}", ""]
     stats = rows(os.path.join(d, "trace", "run_kernel_stats.csv"))
@@ -537,7 +552,8 @@ def config_gpu(name, args, B, torch):
         row = {"workload": describe(cs), "algo": B.ALGO_NAMES[algo],
                "kernel": kernel_label(plan, B),
                "steps": steps, "ms_per_step": ms, "event_ms_per_step": ev_ms,
-               "tflops": flops / (ms * 1e-3) / 1e12, "roofline": roof,
+               "tflops": flops / (ms * 1e-3) / 1e12, "auto": auto_call(dc, algo, steps, args.warmup, flops, B, torch),
+               "roofline": roof,
                "kernel_le_step": None if kern_ms is None else kern_ms <= max(ms, ev_ms) * 1.02,
                "breakdown_ms_per_call": {p: v / 5 for p, v in bd["ms"].items() if p != "pre_analysis"}}
         # the explicit im2col path on the same operation: its packing share of the time
@@ -698,6 +714,7 @@ def main():
     roof["kernel_source"] = kern_src
     roof["traffic"] = load_traffic(args.workload, algo_name)
 
+    auto = auto_call(dc, algo, args.steps, args.warmup, flops, B, torch)
     # explicit im2col baseline on the same workload: pack-phase share
     ne = max(5, args.steps // 5)
     wall_e, _, _ = time_algo(dc, B.CONV2D_ALGO_IM2COL_GEMM, ne, 3, B, torch, B.CONV2D_TIMING_OFF)
@@ -764,6 +781,7 @@ def main():
         "phase_events_overhead_ms_per_step": (wall_ph - wall) * 1e3 / args.steps,
         "fused_phases": bd["fused"],
         "pre_analysis_ms_once": bd["ms"]["pre_analysis"],
+        "auto": auto,
         "explicit_im2col": explicit,
         "winograd": wino,
         "cold_cache_ms_median": cold,

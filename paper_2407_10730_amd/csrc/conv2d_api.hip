@@ -478,7 +478,8 @@ constexpr double kPatchCost[4][PC_N] = {
     {8.6, 1.82, 0.36, 16.5, 0.174, 1.7, 0.0431, 0.559, 0, 1.46, 0.0376, 0.896, 0, 0, 0, 0, 2.63, 1.86},  // fp32, 1x1
 };
 // The implicit plan's calls, by type and source of the GEMM's columns (tap table, tap-major, NHWC;
-// sliced kernel): launch, filter repack, layout reorder and per MB of it, split reduction's unpack
+// sliced kernel): launch, filter repack (a constant, right for filters up to about 1 MB; 4.7 MB take
+// 13 us, so such layers are priced too low), layout reorder and per MB of it, split reduction's unpack
 // and per MB, per 10^6 of tile size x reduction on the busiest CU (first block, further blocks),
 // per further block, per MB of x and y.
 constexpr double kImplicitCost[8][10] = {

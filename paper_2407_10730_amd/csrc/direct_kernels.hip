@@ -1698,11 +1698,12 @@ __global__ __launch_bounds__(256) void dw_nhwc_kernel(DirectArgs A, const TX* __
 // sets (row i of the walk starts output row i and finishes output row i - R + 1), so every index
 // is static in a loop body of R rows.  The products of an output are added in the same order as
 // above, so results are the same bit for bit.
-// Bound by HBM latency at 3 waves per SIMD (146 registers in bf16, 166 in fp32).  2 pixels a thread:
-// 4 take 214 to 240 registers, 2 waves per SIMD.  us per call (filter reorder of about 5 us
-// included), kernel above -> this one: N32 C256 56x56 bf16 40 -> 31 (2.6 -> 3.3 TB/s), 4 pixels 36;
-// fp32 58 -> 49 (4.2 TB/s); N32 C96 112x112 bf16 54 -> 43, fp32 82 -> 71; N32 C672 14x14 bf16
-// 12.7 -> 11.2; small layers, bound by their two launches, the same.
+// Bound by HBM: N32 C256 56x56 bf16 moves 107 MB for 103 in 23 us, 4.7 TB/s or 0.9 of a large copy's
+// rate, at 3 waves per SIMD (146 registers in bf16, 166 in fp32).  2 pixels a thread: 4 take 214 to
+// 240 registers, 2 waves per SIMD.  us per call (filter reorder of about 5 us included), kernel above
+// -> this one: N32 C256 56x56 bf16 39 -> 31, 4 pixels 36; fp32 58 -> 49; N32 C96 112x112 bf16 54 ->
+// 43, fp32 82 -> 71; N32 C672 14x14 bf16 12.7 -> 11.2; small layers, bound by their two launches, the
+// same.
 // 5x5 filters stay above: their 100 filter and 80 sum registers leave one wave per SIMD (N32 C144
 // 56x56 bf16 37 -> 45 us, N32 C672 14x14 20 -> 36).
 constexpr int DWS_PX = 2;

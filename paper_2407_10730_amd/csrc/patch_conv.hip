@@ -23,13 +23,13 @@
 // 56x56 3x3: 3.6e-7, against 4.2e-7 of the fp32 matrix instruction's sums.
 //
 // Measured on MI355X, us per call (filter packing included), gather GEMM -> this kernel: N32 64->64
-// 56x56 3x3 fp32 70 -> 47 (107 -> 158 TFLOP/s), N32 256->512 56x56 1x1 stride 2 fp32 75 -> 67, N32
-// 256->256 56x56 3x3 bf16 162 -> 128 (730 -> 925 TFLOP/s); bf16 layers whose channels the gather had
-// to fetch one by one up to 7x.  What is left of the first (18 us of matrix time): waiting for the
-// patch and the filter operands, about 12 us each, and the split's vector work; of the last (48 us):
-// patch loads 38, filter operands 27, result stores 25 us, partly overlapped (timing variants without
-// them).  An image's first and last blocks hold few chunks, so more of this is start-up than at
-// larger layers.
+// 56x56 3x3 fp32 72 -> 49 (103 -> 150 TFLOP/s), N32 256->512 56x56 1x1 stride 2 fp32 78 -> 68, N32
+// 256->256 56x56 3x3 bf16 168 -> 132 (705 -> 897 TFLOP/s); bf16 layers whose channels the gather had
+// to fetch one by one up to 11x (N16 1744->16 203x64 1x1 stride 2 NHWC 462 -> 42).  Counters of the
+// first and of N32 256->256: matrix unit busy 0.54 of the kernel's cycles, other vector instructions
+// 0.18 and 0.11 (at 4 cycles each), LDS bank conflicts 0.14; waves spend 0.25 of their time waiting for
+// memory, LDS or barriers and 0.55 for a free issue slot, the matrix unit's above all.  x is fetched
+// 2.8 times in the first (73 MB for 26): tiles that share rows run on different XCDs.
 #include <type_traits>
 
 #include "device_common.h"
