@@ -304,6 +304,42 @@ def test_patch_noalloc(monkeypatch, env, dt):
             dc.close()
 
 
+@pytest.mark.parametrize("env", [{"KSPLIT": 1, "TAIL": 0}, {"KSPLIT": 1, "TAIL": 2}, {"KSPLIT": 3}], ids=str)
+@pytest.mark.parametrize("entry", ["fwd", "noalloc"])
+def test_patch_in_a_graph(monkeypatch, entry, env):
+    """A captured call replays with new inputs, eager calls and synchronisations between the replays (the
+    tail split's counters are left at zero by every launch)."""
+    import torch
+    monkeypatch.setenv("CONV2D_PATCH", "1")
+    for k, v in env.items():
+        monkeypatch.setenv("CONV2D_PATCH_" + k, str(v))
+    dc = DeviceConv(_shape(2, 96, 14, 14, 64, 3, 3), "random")
+    call = B.conv2d_fwd if entry == "fwd" else B.conv2d_fwd_noalloc
+    try:
+        assert dc.plan().kernel == B.CONV2D_KERNEL_PATCH
+        y = torch.empty_like(dc.y)
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s):
+            for _ in range(2):  # workspaces exist before the capture, on its stream
+                call(dc.desc, dc.x, dc.w, dc.b, y, B.CONV2D_ALGO_AUTO, s)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            call(dc.desc, dc.x, dc.w, dc.b, y, B.CONV2D_ALGO_AUTO, s)
+        for i in range(4):
+            dc.x.mul_(-1.0 if i % 2 else 0.5)
+            y.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            call(dc.desc, dc.x, dc.w, dc.b, dc.y, B.CONV2D_ALGO_AUTO, s)
+            torch.cuda.synchronize()
+            assert y.any() and torch.equal(y, dc.y)
+    finally:
+        dc.close()
+
+
 def test_patch_breakdown_does_not_depend_on_the_last_call(monkeypatch):
     """IMPLICIT_GEMM's account holds named calls (here with an unpack) and AUTO's patch calls (without):
     its totals and its fused phases are the same whichever ran last."""
